@@ -71,9 +71,9 @@ typedef enum {
 typedef enum { TD_F32 = 0, TD_BF16 = 1 } td_dtype;
 
 /* Attention kernel choice: AUTO = bf16 at head_dim 64, 96 or 128 -> matrix-core (MFMA)
- * kernel, otherwise (fp32, or another head_dim) the vector-ALU kernel.  VALU / MFMA force
- * one (MFMA requires bf16 and head_dim 64, 96 or 128, else td_create returns
- * TD_EUNSUPPORTED). */
+ * kernel, otherwise (fp32, or another head_dim) the fp32 matrix-instruction kernel.  VALU
+ * forces the vector-ALU kernel (the cross-check of both), MFMA the matrix-core kernel
+ * (which requires bf16 and head_dim 64, 96 or 128, else td_create returns TD_EUNSUPPORTED). */
 typedef enum { TD_ATTN_AUTO = 0, TD_ATTN_VALU = 1, TD_ATTN_MFMA = 2 } td_attn_impl;
 
 typedef struct {
@@ -84,9 +84,9 @@ typedef struct {
   int32_t n_layers;     /* L >= 1                                                         */
   int32_t n_q_heads;    /* Hq, a multiple of Hkv                                          */
   int32_t n_kv_heads;   /* Hkv >= 1                                                       */
-  int32_t head_dim;     /* d: a multiple of 32 in [32, 256] (else TD_EINVAL); the matrix- */
-                        /*   core kernels implement 64, 96 and 128, the vector-ALU       */
-                        /*   kernel every d                                              */
+  int32_t head_dim;     /* d: a multiple of 32 in [32, 256] (else TD_EINVAL); the bf16    */
+                        /*   matrix-core kernels implement 64, 96 and 128, the fp32      */
+                        /*   matrix-instruction and vector-ALU kernels every d           */
   int32_t window;       /* sliding window W (0 = dense): key visible iff D - depth < W    */
   int32_t dtype;        /* td_dtype of pools, q, out, k_new, v_new                        */
   int32_t attn_impl;    /* td_attn_impl                                                   */

@@ -10,10 +10,10 @@
 // per-row online softmax.  Groups, waves and (if the node axis is split over WGs) splits
 // are merged by the usual max/sum rescaling.
 //
-// Used for fp32 (cache-resident tiny shapes), for the head dims the matrix-core kernel
-// does not implement (any multiple of 32 up to 256; blocks of 4 rows past d = 128, so that
-// the rows' query and output registers stay within the register file), and as the
-// cross-check of the bf16 matrix-core kernel.
+// Runs where the caller forces it (TD_ATTN_VALU): the cross-check of the bf16 matrix-core
+// kernel and of the fp32 matrix-instruction kernel, which is faster at every size measured.
+// Any head dim that is a multiple of 32 up to 256; blocks of 4 rows past d = 128, so that the
+// rows' query and output registers stay within the register file.
 #include "attn_common.h"
 
 namespace td {

@@ -237,7 +237,7 @@ td_status batch_beam_attn_decode(bbs_ctx* c, int32_t layer_begin, int32_t n_laye
   if (!c->pending && (d_k_new || d_v_new)) return bfail(c, TD_EINVAL, "no K/V is pending (after init): pass NULL k_new / v_new");
   if (c->pending && (!al16(d_k_new) || !al16(d_v_new))) return bfail(c, TD_EINVAL, "k_new / v_new must be 16-byte aligned");
   if (!(scale > 0.0f) || !std::isfinite(scale)) return bfail(c, TD_EINVAL, "scale must be finite and > 0");
-  const bool mfma = s.dtype == TD_BF16 && c->desc.attn_impl != TD_ATTN_VALU && td::mfma_head_dim(s.D);
+  const td::AttnKernel kernel = td::attn_kernel(s, c->desc.attn_impl);
   td::AttnArgs a{};
   a.q = d_q;
   a.k_new = d_k_new;
@@ -248,14 +248,14 @@ td_status batch_beam_attn_decode(bbs_ctx* c, int32_t layer_begin, int32_t n_laye
   a.scale_log2 = scale * 1.4426950408889634f;
   a.kv_pending = c->pending ? 1 : 0;
   a.moves = 0;
-  const int rpb = mfma ? td::attn_mfma_rows_per_block() : td::attn_valu_rows_per_block(s.D);
+  const int rpb = td::attn_rows_per_block(s, kernel);
   a.row_blocks = (s.Hq / s.Hkv + rpb - 1) / rpb;
   a.row_blocks32 = a.row_blocks;
   a.splits = td::attn_choose_splits(s, n_layers, a.row_blocks);
   const long units = (long)s.T * n_layers * s.Hkv * a.row_blocks;
   if (units * a.splits > s.attn_pairs_max && a.splits > 1) a.splits = 1;
   a.xcd_group = 0;
-  hipError_t e = mfma ? td::launch_attn_mfma(s, a, st, nullptr, nullptr) : td::launch_attn_valu(s, a, st, nullptr, nullptr);
+  hipError_t e = td::launch_attn(kernel, s, a, st, nullptr, nullptr);
   if (e == hipSuccess && a.splits > 1) e = td::launch_attn_combine(s, a, rpb, st, nullptr, nullptr);
   if (e != hipSuccess) return bhip(c, e, "batch_beam_attn_decode launch");
   if (c->pending) {

@@ -241,7 +241,8 @@ td_status trie_attn_decode(td_ctx* c, int32_t layer_begin, int32_t n_layers, con
   if (c->pending && (!aligned16(d_k_new) || !aligned16(d_v_new)))
     return fail(c, TD_EINVAL, "k_new / v_new must be 16-byte aligned");
   if (!(scale > 0.0f) || !std::isfinite(scale)) return fail(c, TD_EINVAL, "scale must be finite and > 0");
-  const bool mfma = s.dtype == TD_BF16 && c->desc.attn_impl != TD_ATTN_VALU && td::mfma_head_dim(s.D);
+  const td::AttnKernel kernel = td::attn_kernel(s, c->desc.attn_impl);
+  const bool mfma = kernel == td::AttnKernel::kMfma;
   td::AttnArgs a{};
   a.q = d_q;
   a.k_new = d_k_new;
@@ -251,7 +252,7 @@ td_status trie_attn_decode(td_ctx* c, int32_t layer_begin, int32_t n_layers, con
   a.n_layers = n_layers;
   a.scale_log2 = scale * 1.4426950408889634f;
   a.kv_pending = c->pending ? 1 : 0;
-  const int rpb = mfma ? td::attn_mfma_rows_per_block() : td::attn_valu_rows_per_block(s.D);
+  const int rpb = td::attn_rows_per_block(s, kernel);
   a.row_blocks = (s.b * (s.Hq / s.Hkv) + rpb - 1) / rpb;
   a.row_blocks32 = a.row_blocks;
   if (mfma && a.row_blocks == 2) {  // b G in (32, 64]: one WG over both row blocks
@@ -309,7 +310,7 @@ td_status trie_attn_decode(td_ctx* c, int32_t layer_begin, int32_t n_layers, con
     if (e == hipSuccess) e = hipEventRecord(mv0, st);
     if (e == hipSuccess) e = hipEventRecord(mv1, st);
   }
-  if (e == hipSuccess) e = mfma ? td::launch_attn_mfma(s, a, st, ev0, main_ev1) : td::launch_attn_valu(s, a, st, ev0, main_ev1);
+  if (e == hipSuccess) e = td::launch_attn(kernel, s, a, st, ev0, main_ev1);
   if (e == hipSuccess && a.splits > 1) {
     td::AttnArgs ac = a;  // the combine runs per 32-row block
     ac.row_blocks = a.row_blocks32;

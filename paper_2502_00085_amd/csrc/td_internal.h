@@ -119,8 +119,8 @@ struct AttnArgs {
 
 hipError_t launch_init_prompt(const DevState& s, const int32_t* d_plen, const int32_t* d_tokens,
                               int stride, hipStream_t st);
-// Head dims the matrix-core kernels implement (the vector-ALU kernel takes any multiple of
-// 32 up to 256).
+// Head dims the bf16 matrix-core kernels implement (the others take any multiple of 32 up to
+// 256).
 inline bool mfma_head_dim(int d) { return d == 64 || d == 96 || d == 128; }
 // The launchers take optional kernel-timestamp events (hipExtLaunchKernel): ev0 records
 // the dispatch of the first launched kernel, ev1 the completion of the last (null = none).
@@ -135,6 +135,28 @@ int attn_tree_rows_per_block();
 hipError_t launch_attn_tree(const DevState& s, const AttnArgs& a, hipStream_t st, hipEvent_t ev0,
                             hipEvent_t ev1);
 int attn_valu_rows_per_block(int d);  // query rows per block at head dim d
+hipError_t launch_attn_mfma32(const DevState& s, const AttnArgs& a, hipStream_t st, hipEvent_t ev0,
+                              hipEvent_t ev1);
+int attn_mfma32_rows_per_block(const DevState& s);
+// The decode attention kernel of a context: the bf16 matrix-core one where it is implemented;
+// the fp32 matrix-instruction one for fp32 and the other head dims; the vector-ALU one, the
+// cross-check of both, only where the caller forces it.
+enum class AttnKernel { kMfma, kMfma32, kValu };
+inline AttnKernel attn_kernel(const DevState& s, int attn_impl) {
+  if (attn_impl == TD_ATTN_VALU) return AttnKernel::kValu;
+  return s.dtype == TD_BF16 && mfma_head_dim(s.D) ? AttnKernel::kMfma : AttnKernel::kMfma32;
+}
+inline int attn_rows_per_block(const DevState& s, AttnKernel k) {
+  return k == AttnKernel::kMfma     ? attn_mfma_rows_per_block()
+         : k == AttnKernel::kMfma32 ? attn_mfma32_rows_per_block(s)
+                                    : attn_valu_rows_per_block(s.D);
+}
+inline hipError_t launch_attn(AttnKernel k, const DevState& s, const AttnArgs& a, hipStream_t st, hipEvent_t ev0,
+                              hipEvent_t ev1) {
+  return k == AttnKernel::kMfma     ? launch_attn_mfma(s, a, st, ev0, ev1)
+         : k == AttnKernel::kMfma32 ? launch_attn_mfma32(s, a, st, ev0, ev1)
+                                    : launch_attn_valu(s, a, st, ev0, ev1);
+}
 int attn_choose_splits(const DevState& s, int n_layers, int row_blocks);
 hipError_t launch_logsoftmax_topk(const DevState& s, const float* logits, int32_t* sel_parent,
                                   int32_t* sel_token, float* sel_score, float* sel_logprob,

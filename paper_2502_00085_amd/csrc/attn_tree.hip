@@ -5,23 +5,35 @@
 // on a live path is exactly the ancestor-or-self relation, within the window of depth(q).
 // When many nodes are queries (the prefill of a serialized trie), the decode kernel's
 // layout is wasteful: each 32-row block streams its whole key range through LDS for 32 x
-// 32 scores per tile.  Here a WG of 4 waves holds 128 query rows (wave w: rows 32w ..
+// 32 scores per tile.  Here a group of 4 waves holds 128 query rows (wave w: rows 32w ..
 // 32w + 31, each a (query node, query head) pair of one KV head) and streams the key range
-// once for all of them; two such WGs share a CU (64 KiB of LDS and 256 VGPRs each at
+// once for all of them; two such groups share a CU (64 KiB of LDS and 256 VGPRs each at
 // d = 128), so one computes while the other waits at its tile barrier:
 //
-//   * a tile is 64 keys (two 32-key halves), K and V loaded by the whole WG with direct
+//   * a tile is 64 keys (two 32-key halves), K and V loaded by the whole group with direct
 //     16-byte global -> LDS loads into one of two buffers while the other is consumed;
-//   * per half, each wave computes S^T = K Q^T and O^T += V^T P^T on
+//   * each wave computes S^T = K Q^T and O^T += V^T P^T of both halves on
 //     v_mfma_f32_32x32x16_bf16 with the decode kernel's LDS layout and operand reads;
-//   * visibility: a half whose keys all lie in the shared prefix (every beam's path) and no
+//   * visibility: a tile whose keys all lie in the shared prefix (every beam's path) and no
 //     deeper than any of the wave's queries, and inside every query's window, is fully
-//     visible; otherwise each score is tested against the key's depth and mask, which the
-//     lanes loaded with the tile and exchange by lane permutes;
-//   * a wave skips the halves past its deepest query; each wave owns its rows, so nothing
-//     is merged across waves.
+//     visible; otherwise each score is tested against the key's depth and, past the shared
+//     prefix, its mask, which the lanes loaded with the tile and exchange by lane permutes;
+//   * the softmax shift of a row moves only when its probabilities leave their range, which
+//     their sum (needed anyway) tells: no maximum is taken;
+//   * a wave skips what lies past its deepest query; each wave owns its rows.
+//
+// Launches of few WGs (up to two per CU) make one WG of two groups, which take the tiles in
+// turn and merge their states at the end: the longest block's chain of tiles is halved.
 // The row blocks of one (trie, layer, KV head) are placed on one XCD, so that its K/V rows
 // are read from HBM once and from that XCD's L2 afterwards.
+//
+// What bounds it: at two waves per SIMD neither pipe is full (matrix cores 35 % of the time,
+// vector ALU 42 %); leaving out the loads, the exponentials or most of the output products
+// shortens a tile by little more than their own time, so the waves' chains of score products,
+// softmax and output products are the limit.  A software pipeline of the three (scores of one
+// half beside the softmax of another) measured slower as hipcc schedules it.  Prefill of 2,096
+// nodes at d = 128, 32 q / 8 KV heads, per layer: 85 us -> 62 us in one-layer calls, 50 -> 44 us
+// in a call of 16 layers (782 TFLOP/s); 100 queries in one-layer calls: 68 -> 44 us.
 #include "attn_common.h"
 #include "mfma_tile.h"
 
@@ -32,8 +44,10 @@ namespace {
 constexpr int kTreeWaves = 4;  // (two WGs per CU: their barriers do not wait on each other)
 constexpr int kTreeThreads = kTreeWaves * 64;
 constexpr int kTreeRows = kTreeWaves * 32;  // query rows per WG
+constexpr int kTreeSplitWgs = 512;       // (see launch_attn_tree)
 constexpr float kTreeNegBig = -1.0e30f;
-constexpr float kTreeSlack = 8.0f;  // largest probability 2^8 before a row's shift moves
+constexpr float kTreeSlack = 8.0f;     // a row's shift moves for scores 2^8 above it
+constexpr float kTreeMost = 8192.0f;   // ... once 16 of its probabilities add up to more than this
 
 template <int D>
 struct TreeCfg {
@@ -42,22 +56,39 @@ struct TreeCfg {
   static constexpr int CPR = D / 8;                     // 16-byte chunks per node row
   static constexpr int NBLK = CPR / 4;                  // 64-byte blocks per row
   static constexpr int HALF = 32 * D * 2;               // bytes of 32 K (or V) rows
-  static constexpr int TILE = 4 * HALF;                 // K half 0, K half 1, V half 0, V half 1
-  static constexpr int LOADS = TILE / 16 / kTreeThreads;  // 16-byte loads per thread per tile
-  static_assert(TILE % (16 * kTreeThreads) == 0, "a tile is a whole number of WG loads");
+  static constexpr int LOADS = 2 * HALF / 16 / kTreeThreads;  // 16-byte loads per thread: K (or V) of a tile
+  static_assert(2 * HALF % (16 * kTreeThreads) == 0, "a tile is a whole number of WG loads");
+  // load j of a thread is load 0 moved by whole rows (the same rotation), so one offset does
+  static constexpr bool ONE_OFS = kTreeThreads % CPR == 0 && (kTreeThreads / CPR) % CPR == 0;
+  static constexpr int OFS = ONE_OFS ? 1 : LOADS;
+  static constexpr int WAVES = D == 64 ? 3 : 2;  // per SIMD: as many as the registers allow
+  static constexpr int VROT = 8 % NBLK == 0 ? 1 : 4;  // rotations of V rows 8 apart
 };
 
-template <int D>
-__global__ __launch_bounds__(kTreeThreads, 2) void k_attn_tree(DevState s, AttnArgs a) {
+// XCD order of the row blocks of one (trie, layer, KV head): the deepest (longest) first.  With
+// one unit per XCD every block is resident at once, two per CU: the second half then goes up
+// from the shortest, so that the CU of the longest block gets the shortest beside it.
+__device__ inline int tree_row_block(int k, int nb, bool fold) {
+  return fold && k >= nb / 2 ? k - nb / 2 : nb - 1 - k;
+}
+
+// KS: groups of 4 waves that share the rows and split the keys, tile by tile (group k takes
+// tiles k, k + KS, ...); their states are merged at the end.
+template <int D, int KS>
+__global__ __launch_bounds__(KS * kTreeThreads, TreeCfg<D>::WAVES) void k_attn_tree(DevState s, AttnArgs a) {
   using C = TreeCfg<D>;
-  __shared__ __attribute__((aligned(16))) unsigned char lds[2 * C::TILE];
+  // K and V of two tiles.  Four arrays, each used for one buffer only: the compiler can then
+  // tell an operand read of one buffer from the direct loads under way into the other (with
+  // one array it waits for every load before the first read: no load overlaps its tile).
+  __shared__ __attribute__((aligned(16))) unsigned char kbuf0[KS * 2 * C::HALF], vbuf0[KS * 2 * C::HALF];
+  __shared__ __attribute__((aligned(16))) unsigned char kbuf1[KS * 2 * C::HALF], vbuf1[KS * 2 * C::HALF];
   __shared__ int wred[2][kTreeWaves];  // per wave: deepest query slot + 1, shallowest depth
   // (trie, layer, KV head) unit and row block; the row blocks of a unit go to one XCD
   int x = blockIdx.x, unit, rb;
   if (a.xcd_group) {
     const int xcd = x % 8, k = x / 8;
     unit = (k / a.row_blocks) * 8 + xcd;
-    rb = a.row_blocks - 1 - k % a.row_blocks;
+    rb = tree_row_block(k % a.row_blocks, a.row_blocks, KS == 1 && (int)gridDim.x == 8 * a.row_blocks);
   } else {
     unit = x / a.row_blocks;
     rb = a.row_blocks - 1 - x % a.row_blocks;
@@ -67,7 +98,9 @@ __global__ __launch_bounds__(kTreeThreads, 2) void k_attn_tree(DevState s, AttnA
   const int N = h.n_nodes, base = h.base;
   const int G = s.Hq / s.Hkv;
   const int lab = a.layer_begin + li;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, tid = threadIdx.x % kTreeThreads;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);               // of its group
+  const int group = __builtin_amdgcn_readfirstlane(threadIdx.x / kTreeThreads);
   const int col = lane & 31, hh = lane >> 5;
   const uint64_t* maskp = s.mask + (size_t)t * s.cap + base;
   const int32_t* depthp = s.depth + (size_t)t * s.cap + base;
@@ -84,7 +117,6 @@ __global__ __launch_bounds__(kTreeThreads, 2) void k_attn_tree(DevState s, AttnA
     row_ok = qmask != 0ull;
   }
   if (row_ok) qdepth = depthp[slot];
-  const bool any_dead = __ballot(!row_ok) != 0ull;
   // the wave's deepest query slot, shallowest and deepest query depth (live rows)
   int whi = row_ok ? slot + 1 : 0, wdmin = row_ok ? qdepth : INT_MAX, wdmax = row_ok ? qdepth : -1;
   for (int o = 16; o > 0; o >>= 1) {
@@ -105,46 +137,57 @@ __global__ __launch_bounds__(kTreeThreads, 2) void k_attn_tree(DevState s, AttnA
     hi = max(hi, wred[0][w]);
     dmin = min(dmin, wred[1][w]);
   }
+  hi = __builtin_amdgcn_readfirstlane(hi);
+  dmin = __builtin_amdgcn_readfirstlane(dmin);
   // the block's key range: from the window start of its shallowest query to its deepest
   // query slot (ancestors precede their descendants in slot order)
-  const int lo = hi > 0 ? window_lo(s, t, base, N, dmin) : 0;
+  const int lo = __builtin_amdgcn_readfirstlane(hi > 0 ? window_lo(s, t, base, N, dmin) : 0);
   const int ntiles = hi > lo ? (hi - lo + 63) / 64 : 0;
 
   const __bf16* kpool = static_cast<const __bf16*>(s.k_pool) + pool_row(s, t, lab, g, base);
   const __bf16* vpool = static_cast<const __bf16*>(s.v_pool) + pool_row(s, t, lab, g, base);
 
-  // Load j of this thread writes LDS chunk c = 512 j + threadIdx.x of the tile: part c /
-  // (HALF / 16) (K half 0, K half 1, V half 0, V half 1), row and physical chunk inside it;
-  // K rows rotated by one chunk per row, V rows by one 64-byte block per row (the decode
-  // kernel's layout).  ld[j]: tile row (bits 0-7), element offset of the logical chunk in
-  // its row (bits 8-15), V (bit 16).
-  int ld[C::LOADS];
+  // Load j of this thread writes 16-byte LDS chunk c = j kTreeThreads + tid of its group's
+  // tile's K (and V): tile row c / CPR at physical chunk c % CPR; the K rows of a 32-key half
+  // are rotated by one chunk per row, its V rows by one 64-byte block per row (the decode
+  // kernel's layout).
+  // kofs / vofs: byte offset, in the tile's 64 pool rows, of the logical chunk it loads.
+  uint32_t kofs[C::OFS], vofs[C::OFS];
 #pragma unroll
-  for (int j = 0; j < C::LOADS; ++j) {
-    const int c = j * kTreeThreads + (int)threadIdx.x;
-    const int part = c / (C::HALF / 16), p = c % (C::HALF / 16);
-    const int row = p / C::CPR, pc = p % C::CPR;
-    const bool isv = part >= 2;
-    const int off = isv ? (pc + C::CPR - 4 * (row % C::NBLK)) % C::CPR * 8 : (pc + C::CPR - row % C::CPR) % C::CPR * 8;
-    ld[j] = ((part & 1) * 32 + row) | (off << 8) | (isv ? 1 << 16 : 0);
+  for (int j = 0; j < C::OFS; ++j) {
+    const int c = j * kTreeThreads + tid, row = c / C::CPR, pc = c % C::CPR;
+    kofs[j] = row * (2 * D) + (pc + C::CPR - row % 32 % C::CPR) % C::CPR * 16;
+    vofs[j] = row * (2 * D) + (pc + C::CPR - 4 * (row % 32 % C::NBLK)) % C::CPR * 16;
   }
   // key depth and mask of tile key lane (0..63), for the visibility test
   int kdep = 0;
-  uint64_t kmk = 0;
-  auto issue = [&](int tile, int buf) {
+  uint64_t kmk = ~0ull;
+  auto issue = [&](int tile, unsigned char* kdst, unsigned char* vdst) __attribute__((always_inline)) {
     const int tb = lo + tile * 64;
-    unsigned char* dst = lds + buf * C::TILE;
+    const unsigned char* kt = reinterpret_cast<const unsigned char*>(kpool + (size_t)tb * D);
+    const unsigned char* vt = reinterpret_cast<const unsigned char*>(vpool + (size_t)tb * D);
+    const bool full = tb + 64 <= hi;
+    const uint32_t last = (uint32_t)(hi - 1 - tb) * (2 * D);  // (rows past the end: the last row)
 #pragma unroll
     for (int j = 0; j < C::LOADS; ++j) {
-      const int n = min(tb + (ld[j] & 255), hi - 1);
-      const __bf16* src = ((ld[j] >> 16) ? vpool : kpool) + (size_t)n * D + ((ld[j] >> 8) & 255);
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                       (__attribute__((address_space(3))) void*)(dst + (j * kTreeThreads + wave * 64) * 16),
-                                       16, 0, 0);
+      const uint32_t step = C::ONE_OFS ? j * (kTreeThreads / C::CPR) * 2 * D : 0;
+      uint32_t ko = kofs[C::ONE_OFS ? 0 : j], vo = vofs[C::ONE_OFS ? 0 : j];
+      const unsigned char *kt_ = kt + step, *vt_ = vt + step;
+      if (!full) {
+        const uint32_t krow = (ko + step) / (2 * D) * (2 * D), vrow = (vo + step) / (2 * D) * (2 * D);
+        ko = min(krow, last) + (ko + step - krow);
+        vo = min(vrow, last) + (vo + step - vrow);
+        kt_ = kt;
+        vt_ = vt;
+      }
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(kt_ + ko),
+                                       (__attribute__((address_space(3))) void*)(kdst + (j * kTreeThreads + wave * 64) * 16), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(vt_ + vo),
+                                       (__attribute__((address_space(3))) void*)(vdst + (j * kTreeThreads + wave * 64) * 16), 16, 0, 0);
     }
     const int nn = min(tb + lane, hi - 1);
     kdep = depthp[nn];
-    kmk = maskp[nn];
+    if (tb + 64 > h.n_shared) kmk = maskp[nn];  // (before: every mask is all ones)
   };
 
   // this lane's query row (B operand of S^T): half hh of the row's d range
@@ -159,10 +202,20 @@ __global__ __launch_bounds__(kTreeThreads, 2) void k_attn_tree(DevState s, AttnA
       qv[k] = __builtin_bit_cast(bf16x8, v);
     }
   }
-  // operand geometry (as in the decode kernel): K rows read in MFMA layout; V read back
-  // transposed by 16-lane groups
+  // operand read offsets (as in the decode kernel): K rows in MFMA layout, V transposed by
+  // 16-lane groups
   const int grp = lane >> 4, tm = (lane & 15) >> 2, tq = lane & 3;
-  const int krow = col * (2 * D), kc0 = hh * (C::CPR / 2) + col;  // K operand k: chunk (kc0 + k) % CPR
+  int kread[C::KSTEPS], vread[C::VROT][C::DT];
+#pragma unroll
+  for (int k = 0; k < C::KSTEPS; ++k) kread[k] = col * (2 * D) + (hh * (C::CPR / 2) + col + k) % C::CPR * 16;
+#pragma unroll
+  for (int x8 = 0; x8 < C::VROT; ++x8)
+#pragma unroll
+    for (int dt = 0; dt < C::DT; ++dt) {
+      const int n = 8 * x8 + 4 * hh + tm;
+      const int c = 4 * dt + 2 * (grp & 1) + (tq >> 1);
+      vread[x8][dt] = (4 * hh + tm) * (2 * D) + phys_chunk<C::CPR, C::NBLK>(n, c) * 16 + 8 * (tq & 1);
+    }
 
   const float scale = a.scale_log2;
   const uint32_t qlo = (uint32_t)qmask, qhi = (uint32_t)(qmask >> 32);
@@ -173,119 +226,163 @@ __global__ __launch_bounds__(kTreeThreads, 2) void k_attn_tree(DevState s, AttnA
 #pragma unroll
     for (int v = 0; v < 16; ++v) o[dt][v] = 0.0f;
 
-  if (ntiles > 0) issue(0, 0);
-  for (int tile = 0; tile < ntiles; ++tile) {
-    const int buf = tile & 1;
+  // (tile: the group's tile number)
+  auto step = [&](int tile, const unsigned char* kb, const unsigned char* vb, unsigned char* knext,
+                  unsigned char* vnext) __attribute__((always_inline)) {
     __builtin_amdgcn_s_waitcnt(kWaitVmAll);  // this thread's loads of the tile have landed
     const int cdep = kdep;
     const uint64_t cmk = kmk;
     __syncthreads();  // every thread's loads have landed; the other buffer is free
-    if (tile + 1 < ntiles) issue(tile + 1, buf ^ 1);
+    if (tile + KS < ntiles) issue(tile + KS, knext, vnext);
     const int tb = lo + tile * 64;
-    const unsigned char* kb = lds + buf * C::TILE;
-    const unsigned char* vb = kb + 2 * C::HALF;
-#pragma unroll 1
-    for (int half = 0; half < 2; ++half) {  // (not unrolled: one half's operands live at a time)
-      const int hb = tb + half * 32;  // first key of the half
-      if (hb >= whi) continue;        // (wave-uniform) past the wave's deepest query
-      const unsigned char* kh = kb + half * C::HALF;
-      const __bf16* vh = reinterpret_cast<const __bf16*>(vb + half * C::HALF);
-      bf16x8 kv[C::KSTEPS];
+    if (tb >= whi) return;  // (wave-uniform) past the wave's deepest query
+    // scores of both 32-key halves (two independent chains)
+    f32x16 acc[2];
 #pragma unroll
-      for (int k = 0; k < C::KSTEPS; ++k) kv[k] = *reinterpret_cast<const bf16x8*>(kh + krow + (kc0 + k) % C::CPR * 16);
-      bf16x8 va[2][C::DT];
+    for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0.0f;
 #pragma unroll
-      for (int uu = 0; uu < 2; ++uu) {
+    for (int k = 0; k < C::KSTEPS; ++k)
 #pragma unroll
-        for (int dt = 0; dt < C::DT; ++dt) {
-          i16x4 part[2];
+      for (int half = 0; half < 2; ++half)
+        acc[half] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            *reinterpret_cast<const bf16x8*>(kb + half * C::HALF + kread[k]), qv[k], acc[half], 0, 0, 0);
+    // visibility of this lane's keys tb + 32 half + 8(v/4) + 4hh + v%4 for its row.  Depth never
+    // decreases along the slots, so the tile's depth range is that of its first and last key.
+    const int dfirst = __builtin_amdgcn_readlane(cdep, 0), dlast = __builtin_amdgcn_readlane(cdep, 63);
+    const bool all_visible = tb + 64 <= hi && tb + 64 <= h.n_shared && dlast <= wdmin &&
+                             (s.W <= 0 || wdmax - dfirst < s.W);
+    if (!all_visible) {
+      // (branch-free per key: the test only selects)
+      uint32_t vis[2] = {0, 0};
+      if (tb + 64 <= h.n_shared) {
+        // every key lies on every beam's path: the depth alone decides (the diagonal of a prefill)
 #pragma unroll
-          for (int hf = 0; hf < 2; ++hf) {
-            const int n = 16 * uu + 8 * hf + 4 * hh + tm;
-            const int c = 4 * dt + 2 * (grp & 1) + (tq >> 1);
-            const int pc = phys_chunk<C::CPR, C::NBLK>(n, c);
-            part[hf] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(vh + n * D + pc * 8 + 4 * (tq & 1)));
-          }
-          va[uu][dt] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(part[0], part[1], 0, 1, 2, 3, 4, 5, 6, 7));
-        }
-      }
-      f32x16 acc;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-#pragma unroll
-      for (int k = 0; k < C::KSTEPS; ++k) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kv[k], qv[k], acc, 0, 0, 0);
-
-      // visibility of this lane's keys hb + 8(v/4) + 4hh + v%4 for its row.  Depth never
-      // decreases along the slots, so the half's depth range is that of its first and last
-      // key (lanes 32 half and 32 half + 31 hold them).
-      const int dfirst = __builtin_amdgcn_readlane(cdep, 32 * half);
-      const int dlast = __builtin_amdgcn_readlane(cdep, 32 * half + 31);
-      const bool all_visible = hb + 32 <= hi && hb + 32 <= h.n_shared && dlast <= wdmin &&
-                               (s.W <= 0 || wdmax - dfirst < s.W);
-      if (all_visible) {
-        if (any_dead) {
-#pragma unroll
-          for (int v = 0; v < 16; ++v) acc[v] = row_ok ? acc[v] : -INFINITY;
+        for (int v = 0; v < 32; ++v) {
+          const int i = 32 * (v >> 4) + 8 * (v % 16 >> 2) + 4 * hh + (v & 3);
+          const int dn = __builtin_amdgcn_ds_bpermute(i << 2, cdep);
+          const bool ok = (tb + i < hi) & (dn <= qdepth) & ((s.W <= 0) | (qdepth - dn < s.W));
+          vis[v >> 4] |= (uint32_t)ok << (v & 15);
         }
       } else {
-        // (branch-free: the test only selects)
         const int mlo = (int)(uint32_t)cmk, mhi = (int)(uint32_t)(cmk >> 32);
-        uint32_t vis = 0;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int i = 32 * half + 8 * (v >> 2) + 4 * hh + (v & 3);
+        for (int v = 0; v < 32; ++v) {
+          const int i = 32 * (v >> 4) + 8 * (v % 16 >> 2) + 4 * hh + (v & 3);
           const int dn = __builtin_amdgcn_ds_bpermute(i << 2, cdep);
           const uint32_t lo_ = (uint32_t)__builtin_amdgcn_ds_bpermute(i << 2, mlo);
           const uint32_t hi_ = (uint32_t)__builtin_amdgcn_ds_bpermute(i << 2, mhi);
           const bool ok = (tb + i < hi) & (dn <= qdepth) & ((lo_ & qlo) == qlo) & ((hi_ & qhi) == qhi) &
                           ((s.W <= 0) | (qdepth - dn < s.W));
-          vis |= (uint32_t)ok << v;
+          vis[v >> 4] |= (uint32_t)ok << (v & 15);
         }
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[v] = (vis >> v) & 1u ? acc[v] : -INFINITY;
       }
-      float tmax = acc[0];
 #pragma unroll
-      for (int v = 1; v < 16; ++v) tmax = fmaxf(tmax, acc[v]);
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 32)) * scale;
-      // The row's shift m moves up only when a score exceeds it by more than kTreeSlack
-      // (log2 units): the probabilities stay <= 2^kTreeSlack, and O and l are rescaled on
-      // few tiles instead of on nearly every one (softmax does not depend on the shift).
-      const bool raise = tmax > m + kTreeSlack;
-      float alpha = 1.0f;
-      if (__any(raise)) {
-        const float mn = raise ? tmax : m;
-        alpha = __builtin_amdgcn_exp2f(m - mn);
+      for (int half = 0; half < 2; ++half)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[half][v] = (vis[half] >> v) & 1u ? acc[half][v] : -INFINITY;
+    }
+    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      if (half == 1 && tb + 32 >= whi) return;  // (wave-uniform) past the wave's deepest query
+      // Probabilities relative to the row's shift m, rounded to bf16, and their sum over this
+      // lane's 16 keys.  Softmax does not depend on the shift, so it needs no maximum: it only
+      // has to keep the probabilities in range, and their sum says when it does not (a first
+      // tile, or scores far above every earlier one).
+      bf16x8 pb[2];
+      float ps = 0.0f;
+      auto weights = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          pb[v >> 3][v & 7] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(acc[half][v], scale, -m));
+        ps = 0.0f;
+#pragma unroll
+        for (int v = 0; v < 16; v += 2) {
+          const bf16x2 pair = {pb[v >> 3][v & 7], pb[v >> 3][(v & 7) + 1]};
+          ps = __builtin_amdgcn_fdot2_f32_bf16(pair, ones, ps, false);
+        }
+      };
+      weights();
+      if (__any(ps > kTreeMost)) {
+        // raise the shift of the rows that need it to their largest score (a sum above
+        // kTreeMost holds a probability above 2^kTreeSlack)
+        float tmax = acc[half][0];
+#pragma unroll
+        for (int v = 1; v < 16; ++v) tmax = fmaxf(tmax, acc[half][v]);
+        tmax = fmaxf(tmax, __shfl_xor(tmax, 32)) * scale;
+        const float mn = tmax > m + kTreeSlack ? tmax : m;
+        const float alpha = __builtin_amdgcn_exp2f(m - mn);
         m = mn;
+        lsum *= alpha;
 #pragma unroll
         for (int dt = 0; dt < C::DT; ++dt)
 #pragma unroll
           for (int v = 0; v < 16; ++v) o[dt][v] *= alpha;
+        weights();
       }
-      const float mn = m;
-      bf16x8 pb[2];
-#pragma unroll
-      for (int v = 0; v < 16; ++v) pb[v >> 3][v & 7] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(acc[v], scale, -mn));
-      float ps = 0.0f;
-      const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-#pragma unroll
-      for (int v = 0; v < 16; v += 2) {
-        const bf16x2 pair = {pb[v >> 3][v & 7], pb[v >> 3][(v & 7) + 1]};
-        ps = __builtin_amdgcn_fdot2_f32_bf16(pair, ones, ps, false);
-      }
-      lsum = lsum * alpha + ps;
+      lsum += ps;
 #pragma unroll
       for (int uu = 0; uu < 2; ++uu)
 #pragma unroll
-        for (int dt = 0; dt < C::DT; ++dt)
-          o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[uu][dt], pb[uu], o[dt], 0, 0, 0);
+        for (int dt = 0; dt < C::DT; ++dt) {
+          const unsigned char* vp = vb + half * C::HALF + 16 * uu * (2 * D);
+          const i16x4 p0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(vp + vread[2 * uu % C::VROT][dt]));
+          const i16x4 p1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+              (lds_i16x4*)(vp + 8 * (2 * D) + vread[(2 * uu + 1) % C::VROT][dt]));
+          const bf16x8 va = __builtin_bit_cast(bf16x8, __builtin_shufflevector(p0, p1, 0, 1, 2, 3, 4, 5, 6, 7));
+          o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb[uu], o[dt], 0, 0, 0);
+        }
+    }
+  };
+  unsigned char* const kb0 = kbuf0 + group * 2 * C::HALF;
+  unsigned char* const kb1 = kbuf1 + group * 2 * C::HALF;
+  unsigned char* const vb0 = vbuf0 + group * 2 * C::HALF;
+  unsigned char* const vb1 = vbuf1 + group * 2 * C::HALF;
+  if (group < ntiles) issue(group, kb0, vb0);
+  const int steps = (ntiles + KS - 1) / KS;  // (every group takes every step's barrier)
+  for (int i = 0; i < steps; i += 2) {
+    step(i * KS + group, kb0, vb0, kb1, vb1);
+    if (i + 1 < steps) step((i + 1) * KS + group, kb1, vb1, kb0, vb0);
+  }
+
+  if constexpr (KS == 2) {
+    // group 1 hands its state over through LDS, lane by lane (O: [wave][register][lane] in the K
+    // buffers, d / 2 registers each, then m and l in a V buffer)
+    __syncthreads();  // every wave has read its last tile
+    float* const olds0 = reinterpret_cast<float*>(kbuf0);
+    float* const olds1 = reinterpret_cast<float*>(kbuf1);
+    float* const ml = reinterpret_cast<float*>(vbuf0);
+    static_assert(kTreeWaves * 64 * (D / 4) * 4 <= 2 * 2 * C::HALF, "half of O fits a K buffer");
+    if (group == 1) {
+#pragma unroll
+      for (int x = 0; x < D / 4; ++x) {
+        const int at = (wave * (D / 4) + x) * 64 + lane;
+        olds0[at] = o[x / 16][x % 16];
+        olds1[at] = o[(x + D / 4) / 16][(x + D / 4) % 16];
+      }
+      ml[(wave * 2) * 64 + lane] = m;
+      ml[(wave * 2 + 1) * 64 + lane] = lsum;
+    }
+    __syncthreads();
+    if (group == 1) return;
+    const float m1 = ml[(wave * 2) * 64 + lane], l1 = ml[(wave * 2 + 1) * 64 + lane];
+    const float mn = fmaxf(m, m1);
+    const float f0 = __builtin_amdgcn_exp2f(m - mn), f1 = __builtin_amdgcn_exp2f(m1 - mn);
+    lsum = lsum * f0 + l1 * f1;
+#pragma unroll
+    for (int x = 0; x < D / 4; ++x) {
+      const int at = (wave * (D / 4) + x) * 64 + lane;
+      o[x / 16][x % 16] = o[x / 16][x % 16] * f0 + olds0[at] * f1;
+      const int y = x + D / 4;
+      o[y / 16][y % 16] = o[y / 16][y % 16] * f0 + olds1[at] * f1;
     }
   }
 
   // each wave writes its own rows: O / l (zero for a row without keys or without a query)
   lsum += __shfl_xor(lsum, 32);
   if (r < a.qmax * G) {
-    const float inv = row_ok && lsum > 0.0f ? 1.0f / lsum : 0.0f;
+    const bool some = row_ok && lsum > 0.0f;
+    const float inv = some ? 1.0f / lsum : 0.0f;
     __bf16* orow = static_cast<__bf16*>(a.out) +
                    ((((size_t)li * s.T + t) * a.qmax + owner) * s.Hq + g * G + r % G) * D;
 #pragma unroll
@@ -294,7 +391,7 @@ __global__ __launch_bounds__(kTreeThreads, 2) void k_attn_tree(DevState s, AttnA
       for (int q4 = 0; q4 < 4; ++q4) {
         bf16x4 y;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) y[e] = (__bf16)(o[dt][4 * q4 + e] * inv);
+        for (int e = 0; e < 4; ++e) y[e] = (__bf16)(some ? o[dt][4 * q4 + e] * inv : 0.0f);
         *reinterpret_cast<bf16x4*>(orow + 32 * dt + 8 * q4 + 4 * hh) = y;
       }
   }
@@ -304,15 +401,25 @@ __global__ __launch_bounds__(kTreeThreads, 2) void k_attn_tree(DevState s, AttnA
 
 int attn_tree_rows_per_block() { return kTreeRows; }
 
+// Two groups per WG where one group per WG leaves CUs with less than two (measured, a call of
+// 32 WGs: 53 us with one group, 44 with two; of 320 WGs at d = 96: 32 and 28; beyond one round
+// of single groups the two-group WG, whose barrier ties 8 waves, loses: 64 against 71 us for
+// 528 WGs).
 hipError_t launch_attn_tree(const DevState& s, const AttnArgs& a, hipStream_t st, hipEvent_t ev0,
                             hipEvent_t ev1) {
-  const dim3 grid(s.T * a.n_layers * s.Hkv * a.row_blocks), block(kTreeThreads);
+  const int wgs = s.T * a.n_layers * s.Hkv * a.row_blocks;
+  const bool split = wgs <= kTreeSplitWgs;
+  const dim3 grid(wgs), block(split ? 2 * kTreeThreads : kTreeThreads);
+#define LAUNCH_TREE(DD)                                                                               \
+  (split ? hipExtLaunchKernelGGL((k_attn_tree<DD, 2>), grid, block, 0, st, ev0, ev1, 0, s, a)          \
+         : hipExtLaunchKernelGGL((k_attn_tree<DD, 1>), grid, block, 0, st, ev0, ev1, 0, s, a))
   switch (s.D) {
-    case 64: hipExtLaunchKernelGGL(k_attn_tree<64>, grid, block, 0, st, ev0, ev1, 0, s, a); break;
-    case 96: hipExtLaunchKernelGGL(k_attn_tree<96>, grid, block, 0, st, ev0, ev1, 0, s, a); break;
-    case 128: hipExtLaunchKernelGGL(k_attn_tree<128>, grid, block, 0, st, ev0, ev1, 0, s, a); break;
+    case 64: LAUNCH_TREE(64); break;
+    case 96: LAUNCH_TREE(96); break;
+    case 128: LAUNCH_TREE(128); break;
     default: return hipErrorInvalidValue;
   }
+#undef LAUNCH_TREE
   return hipGetLastError();
 }
 

@@ -26,10 +26,10 @@ __device__ inline void store8(__bf16* p, const float* v) {
 }
 
 // Grid: (trie, layer, KV head, row block) units x parts; each (row, 8-element chunk of d)
-// is merged by TP adjacent lanes (TP = 2 beyond 8 splits), lane j taking the groups of 8
+// is merged by TP adjacent lanes (TP = 2 beyond 8 splits, 4 beyond 16), lane j taking the groups of 8
 // splits j, j + TP, ...: every load of a group (maxima, sums and 8-element O chunks) is
 // issued before any is used, so a merge of up to 8 TP splits is one memory round; groups
-// are merged with a running max, and the TP lanes' states with one lane exchange.  WGs of
+// are merged with a running max, and the TP lanes' states pairwise with lane exchanges.  WGs of
 // one wave: a CU issues vector loads at a limited rate, small WGs spread the merge's reads
 // over more CUs.  A split that attended no node (sum 0: an empty range, every node
 // hidden, or a split the span did not need) weighs nothing.
@@ -50,7 +50,7 @@ __global__ __launch_bounds__(kCombineThreads) void k_attn_combine(DevState s, At
   const int D = s.D;
   const int CH = D / 8;
   const int n_live = s.hdr[t].n_live;
-  // (both lanes of an item leave together, or neither)
+  // (the lanes of an item leave together, or none)
   if (item >= R * CH) return;
   const int i = item / CH, c = (item % CH) * 8;
   const int rr = rb * R + i;
@@ -94,19 +94,24 @@ __global__ __launch_bounds__(kCombineThreads) void k_attn_combine(DevState s, At
     }
     M = Mg;
   }
-  if constexpr (TP == 2) {
-    // the other lane's state (its groups), rescaled to the common max; the same order on
-    // both lanes
-    const float M2 = __shfl_xor(M, 1), L2 = __shfl_xor(L, 1);
-    float O2[8];
+  if constexpr (TP > 1) {
+    // the other lanes' states (their groups), rescaled to the common max; the same order on
+    // both lanes of a pair
 #pragma unroll
-    for (int e = 0; e < 8; ++e) O2[e] = __shfl_xor(O[e], 1);
-    const float Mn = fmaxf(M, M2);
-    const float f0 = exp2f((sub == 0 ? M : M2) - Mn), f1 = exp2f((sub == 0 ? M2 : M) - Mn);
-    const float La = sub == 0 ? L : L2, Lb = sub == 0 ? L2 : L;
-    L = La * f0 + Lb * f1;
+    for (int w = 1; w < TP; w <<= 1) {
+      const float M2 = __shfl_xor(M, w), L2 = __shfl_xor(L, w);
+      float O2[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) O[e] = (sub == 0 ? O[e] : O2[e]) * f0 + (sub == 0 ? O2[e] : O[e]) * f1;
+      for (int e = 0; e < 8; ++e) O2[e] = __shfl_xor(O[e], w);
+      const bool low = (sub & w) == 0;
+      const float Mn = fmaxf(M, M2);
+      const float f0 = exp2f((low ? M : M2) - Mn), f1 = exp2f((low ? M2 : M) - Mn);
+      const float La = low ? L : L2, Lb = low ? L2 : L;
+      L = La * f0 + Lb * f1;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) O[e] = (low ? O[e] : O2[e]) * f0 + (low ? O2[e] : O[e]) * f1;
+      M = Mn;
+    }
     if (sub != 0) return;
   }
   const int bm = rr / G;
@@ -121,16 +126,14 @@ __global__ __launch_bounds__(kCombineThreads) void k_attn_combine(DevState s, At
 
 hipError_t launch_attn_combine(const DevState& s, const AttnArgs& a, int rows_per_block, hipStream_t st,
                                hipEvent_t ev0, hipEvent_t ev1) {
-  const int tp = a.splits > 8 ? 2 : 1;  // (two lanes per output chunk beyond 8 splits)
+  const int tp = a.splits > 16 ? 4 : a.splits > 8 ? 2 : 1;  // lanes per output chunk: 8 splits each
   const int parts = (rows_per_block * (s.D / 8) * tp + kCombineThreads - 1) / kCombineThreads;
   const dim3 grid(s.T * a.n_layers * s.Hkv * a.row_blocks * parts);
-  if (s.dtype == TD_F32) {
-    if (tp == 2) hipExtLaunchKernelGGL((k_attn_combine<float, 2>), grid, dim3(kCombineThreads), 0, st, ev0, ev1, 0, s, a, rows_per_block, parts);
-    else hipExtLaunchKernelGGL((k_attn_combine<float, 1>), grid, dim3(kCombineThreads), 0, st, ev0, ev1, 0, s, a, rows_per_block, parts);
-  } else {
-    if (tp == 2) hipExtLaunchKernelGGL((k_attn_combine<__bf16, 2>), grid, dim3(kCombineThreads), 0, st, ev0, ev1, 0, s, a, rows_per_block, parts);
-    else hipExtLaunchKernelGGL((k_attn_combine<__bf16, 1>), grid, dim3(kCombineThreads), 0, st, ev0, ev1, 0, s, a, rows_per_block, parts);
-  }
+#define LAUNCH_COMBINE(T, TP) \
+  hipExtLaunchKernelGGL((k_attn_combine<T, TP>), grid, dim3(kCombineThreads), 0, st, ev0, ev1, 0, s, a, rows_per_block, parts)
+  if (s.dtype == TD_F32) tp == 4 ? LAUNCH_COMBINE(float, 4) : tp == 2 ? LAUNCH_COMBINE(float, 2) : LAUNCH_COMBINE(float, 1);
+  else tp == 4 ? LAUNCH_COMBINE(__bf16, 4) : tp == 2 ? LAUNCH_COMBINE(__bf16, 2) : LAUNCH_COMBINE(__bf16, 1);
+#undef LAUNCH_COMBINE
   return hipGetLastError();
 }
 

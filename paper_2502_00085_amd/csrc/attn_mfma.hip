@@ -26,6 +26,7 @@
 // with max/sum rescaling through LDS; node splits over WGs write partials that a second
 // launch merges (attn_combine.hip).  Template variants: TREE (rows are arbitrary query
 // nodes) and RB = 2 (one WG over two 32-row blocks).
+#include <algorithm>
 #include <type_traits>
 
 #include "attn_common.h"
@@ -87,8 +88,12 @@ struct MfmaCfg {
 // at G = 4) one WG takes both blocks: each wave's tile serves 64 rows, instead of two WGs
 // streaming the same nodes side by side.
 //
-// NW = 4 (decode launches of more WGs than CUs): WGs of 4 waves, two per CU, so that one
-// WG's prologue and merge, when it streams nothing, overlap the other WG's tile stream.
+// NW = 4 (split launches, and unsplit decode launches of more WGs than CUs): WGs of 4 waves, two
+// per CU.  In a launch of several rounds one WG's prologue and merge, when it streams nothing,
+// overlap the other WG's tile stream.  In a split launch a wave has one tile, and what bounds
+// the call is how fast a CU can issue its loads: 8 waves of one WG took 2.4 us (median; 4.6 us
+// the last) to issue 128 KiB and 1.2 us to store their outputs for the merge; half-size WGs
+// spread the same tiles over twice the CUs.
 // With two row blocks, tiles and Q alone fill their LDS (no staging of moved or leaf rows,
 // no fused row copy); with one row block 12 KiB are left to stage rows.
 //
@@ -101,7 +106,7 @@ struct MfmaCfg {
 template <int D, int NW, bool TREE, int RB, bool NT>
 __global__ __launch_bounds__(NW * 64, 2) void k_attn_mfma(DevState s, AttnArgs a) {
   static_assert(RB == 1 || (RB == 2 && !TREE), "two row blocks per WG: decode only");
-  static_assert(NW == 8 || (NW == 4 && !TREE), "4-wave WGs: decode only");
+  static_assert(NW == 8 || NW == 4, "WGs of 4 or 8 waves");
   static_assert(!(NT && TREE), "tree launches share keys between row blocks");
   constexpr int kTileCpol = NT ? 2 : 0;  // cache-policy bits of the tile loads (2: nt)
   using C = MfmaCfg<D, NW>;
@@ -126,7 +131,10 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_mfma(DevState s, AttnArgs a
   int qdepth = -1;  // (TREE) no key is visible to a row without a live query node
   int lo, n0, n1, act;
   if constexpr (TREE) {
-    __shared__ int qrange[2];  // the block's key range end, its shallowest query depth
+    // the block's key range end, its shallowest query depth (past the tiles: a wave may issue its
+    // first tile before another has read them)
+    static_assert(C::MOVE0 + 128 <= C::LDS, "room past the tiles and the merge buffers");
+    int* qrange = reinterpret_cast<int*>(lds + C::MOVE0);
     int slot = r < a.qmax * G ? a.qslots[(size_t)u.t * a.qmax + owner] : -1;
     row_ok = slot >= 0 && slot < N;
     if (row_ok) {
@@ -147,7 +155,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_mfma(DevState s, AttnArgs a
     }
     __syncthreads();
     const int hi = qrange[0];
-    lo = hi > 0 ? window_lo(s, u.t, base, N, qrange[1]) : 0;
+    lo = hi > 0 ? window_lo(s, u.t, base, N, qrange[1], qrange + 2) : 0;
     const int span = max(0, hi - lo);
     const int per = split_range(span, a.splits, NW, a.all_splits, &act);
     n0 = lo + u.split * per;
@@ -707,6 +715,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_mfma(DevState s, AttnArgs a
 }
 
 constexpr int kNW = 8;
+constexpr int kCUs = 256;
 
 }  // namespace
 
@@ -722,6 +731,26 @@ int attn_choose_splits(const DevState& s, int n_layers, int row_blocks) {
   return sp > 16 ? 16 : sp;  // (the kernel activates only the splits its node span needs)
 }
 
+// The bf16 kernel's splits and WGs.  max_nodes, the host's bound on a trie's nodes, says how many
+// WGs a span can use (a trie that fits one WG needs no partials and no merge launch).  8-wave
+// WGs, one per CU, never more than the CUs (264 of them ran two rounds; 24 draft nodes in 11
+// splits of 24 units: 17.9 us, in 10: 17.7).  Where they would leave half of the CUs idle, 4-wave
+// WGs instead (8 units of 2,140 nodes: 9 WGs each, 14.1 us; 17 half-size WGs, 12.9), but not
+// where all CUs are busy: there the smaller WGs only make more partials (32 units of 2,700 nodes,
+// 8 splits: 16.7 us; 16 half-size ones: 19.2).  Past 128 units two 8-wave WGs each do not fit
+// one round: 4-wave ones.
+AttnSplits attn_mfma_splits(const DevState& s, int n_layers, int row_blocks, int row_blocks32, long max_nodes) {
+  const long units = (long)s.T * n_layers * s.Hkv * row_blocks;
+  if (units >= 192) return {1, false};
+  const long tiles = (max_nodes + 31) / 32, fit = s.attn_pairs_max / (units / row_blocks * row_blocks32);
+  auto best = [&](long wgs, long most, int nw) {
+    const long need = std::max((tiles + nw - 1) / nw, std::min(8l, (tiles + nw / 2 - 1) / (nw / 2)));
+    return std::max(1l, std::min({wgs / units, need, fit, most}));
+  };
+  const long full = best(kCUs, 16, kNW), half = best(2 * kCUs, 32, kNW / 2);
+  return units * full < kCUs / 2 || units > kCUs / 2 ? AttnSplits{(int)half, half > 1} : AttnSplits{(int)full, false};
+}
+
 hipError_t launch_attn_mfma(const DevState& s, const AttnArgs& a, hipStream_t st, hipEvent_t ev0,
                             hipEvent_t ev1) {
   // (32-row blocks: row_blocks32 = row_blocks WGs of rb_per_wg blocks each, the last
@@ -729,12 +758,16 @@ hipError_t launch_attn_mfma(const DevState& s, const AttnArgs& a, hipStream_t st
   if (a.rb_per_wg < 1 || a.rb_per_wg > 2 || (a.rb_per_wg == 2 && a.tree) ||
       a.row_blocks32 > a.row_blocks * a.rb_per_wg || a.row_blocks32 <= (a.row_blocks - 1) * a.rb_per_wg)
     return hipErrorInvalidValue;
-  if (a.half_wgs && (a.tree || a.xcd_group || (a.rb_per_wg == 2 && a.moves))) return hipErrorInvalidValue;
+  if (a.half_wgs && a.rb_per_wg == 2 && a.moves) return hipErrorInvalidValue;
   const dim3 grid(s.T * a.n_layers * s.Hkv * a.row_blocks * a.splits), block(kNW * 64), half(kNW * 32);
 #define LAUNCH_MFMA(DD)                                                                                      \
-  (a.tree ? hipExtLaunchKernelGGL((k_attn_mfma<DD, kNW, true, 1, false>), grid, block, 0, st, ev0, ev1, 0, s, a) \
+  (a.tree && a.half_wgs                                                                                        \
+       ? hipExtLaunchKernelGGL((k_attn_mfma<DD, kNW / 2, true, 1, false>), grid, half, 0, st, ev0, ev1, 0, s, a) \
+   : a.tree ? hipExtLaunchKernelGGL((k_attn_mfma<DD, kNW, true, 1, false>), grid, block, 0, st, ev0, ev1, 0, s, a) \
    : a.half_wgs && a.rb_per_wg == 2                                                                            \
        ? hipExtLaunchKernelGGL((k_attn_mfma<DD, kNW / 2, false, 2, true>), grid, half, 0, st, ev0, ev1, 0, s, a) \
+   : a.half_wgs && a.xcd_group                                                                                 \
+       ? hipExtLaunchKernelGGL((k_attn_mfma<DD, kNW / 2, false, 1, false>), grid, half, 0, st, ev0, ev1, 0, s, a) \
    : a.half_wgs                                                                                                \
        ? hipExtLaunchKernelGGL((k_attn_mfma<DD, kNW / 2, false, 1, true>), grid, half, 0, st, ev0, ev1, 0, s, a) \
    : a.rb_per_wg == 2                                                                                          \

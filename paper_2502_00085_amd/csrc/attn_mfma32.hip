@@ -24,6 +24,7 @@
 // K goes HBM -> the wave's LDS tile by direct loads, V HBM -> registers.  The next tile's K is
 // requested once this one's scores are done, its V once this one's products are: with two
 // waves per SIMD one wave's loads overlap the other's matrix work.
+#include <algorithm>
 #include <type_traits>
 
 #include "attn_common.h"
@@ -458,6 +459,12 @@ hipError_t launch_rt(const DevState& s, const AttnArgs& a, dim3 grid, hipStream_
 
 // 32 query rows per WG, or 16 when there are no more.
 int attn_mfma32_rows_per_block(const DevState& s) { return s.b * (s.Hq / s.Hkv) <= 16 ? 16 : 32; }
+
+// (a trie of at most one tile per wave of a WG needs no split, no partials and no merge launch)
+int attn_mfma32_splits(const DevState& s, int n_layers, int row_blocks, long max_nodes) {
+  const long need = (max_nodes + 8 * kTile32 - 1) / (8 * kTile32);
+  return (int)std::max(1l, std::min<long>(attn_choose_splits(s, n_layers, row_blocks), need));
+}
 
 hipError_t launch_attn_mfma32(const DevState& s, const AttnArgs& a, hipStream_t st, hipEvent_t ev0,
                               hipEvent_t ev1) {

@@ -251,10 +251,12 @@ td_status batch_beam_attn_decode(bbs_ctx* c, int32_t layer_begin, int32_t n_laye
   const int rpb = td::attn_rows_per_block(s, kernel);
   a.row_blocks = (s.Hq / s.Hkv + rpb - 1) / rpb;
   a.row_blocks32 = a.row_blocks;
-  a.splits = td::attn_choose_splits(s, n_layers, a.row_blocks);
+  const td::AttnSplits sp = td::attn_splits(kernel, s, n_layers, a.row_blocks, a.row_blocks32, s.cap);
+  a.splits = sp.splits;
   const long units = (long)s.T * n_layers * s.Hkv * a.row_blocks;
   if (units * a.splits > s.attn_pairs_max && a.splits > 1) a.splits = 1;
   a.xcd_group = 0;
+  a.half_wgs = a.splits > 1 && sp.half_wgs;
   hipError_t e = td::launch_attn(kernel, s, a, st, nullptr, nullptr);
   if (e == hipSuccess && a.splits > 1) e = td::launch_attn_combine(s, a, rpb, st, nullptr, nullptr);
   if (e != hipSuccess) return bhip(c, e, "batch_beam_attn_decode launch");

@@ -1,4 +1,5 @@
 // Host side of the C ABI: argument checks, context lifetime, state read/load, launches.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -21,6 +22,8 @@ struct td_ctx {
                                        //   (for the layers not yet written)
   std::vector<int32_t> leaf_depth;     // per trie: depth of its live leaves (mirrors the
                                        //   device header; tells which appends collect)
+  std::vector<int32_t> nodes;          // per trie: an upper bound of its stored nodes (exact after
+                                       //   init_prompt, load_state and read_state)
   int32_t* d_plen = nullptr;
   int splits_override = 0;             // TD_ATTN_SPLITS (tuning): WGs per attention unit
   hipEvent_t ev[4][2] = {};             // td_set_kernel_events: per td_phase, the
@@ -69,6 +72,13 @@ td_status check_ready(td_ctx* c) {
   for (size_t t = 0; t < c->inited.size(); ++t)
     if (!c->inited[t]) return fail(c, TD_ESTATE, "trie %zu is not initialised", t);
   return TD_OK;
+}
+
+// A bound on the nodes of any trie of the context (what an attention call may have to read).
+long max_nodes(const td_ctx* c) {
+  long n = 0;
+  for (int32_t x : c->nodes) n = n > x ? n : x;
+  return n;
 }
 
 }  // namespace
@@ -184,6 +194,7 @@ td_status td_create(const td_desc* d, td_ctx** out) {
   }
   c->inited.assign(s.T, 0);
   c->leaf_depth.assign(s.T, 0);
+  c->nodes.assign(s.T, 0);
   c->layer_written.assign(s.L, 0);
   if (const char* sp = getenv("TD_ATTN_SPLITS")) c->splits_override = atoi(sp) > 0 ? (atoi(sp) < 64 ? atoi(sp) : 64) : 0;
   *out = c;
@@ -218,7 +229,10 @@ td_status td_init_prompt(td_ctx* c, const int32_t* h_plen, const int32_t* d_toke
   if (e == hipSuccess) e = hipMemset(c->dev.fin_done, 0, sizeof(int32_t) * c->dev.T);
   if (e != hipSuccess) return hip_fail(c, e, "td_init_prompt");
   c->inited.assign(c->dev.T, 1);
-  for (int t = 0; t < c->dev.T; ++t) c->leaf_depth[t] = h_plen[t] - 1;
+  for (int t = 0; t < c->dev.T; ++t) {
+    c->leaf_depth[t] = h_plen[t] - 1;
+    c->nodes[t] = h_plen[t];
+  }
   c->pending = c->moves_pending = false;
   c->layer_written.assign(c->dev.L, 0);
   return TD_OK;
@@ -259,7 +273,8 @@ td_status trie_attn_decode(td_ctx* c, int32_t layer_begin, int32_t n_layers, con
     a.rb_per_wg = 2;
     a.row_blocks = 1;
   }
-  a.splits = c->splits_override > 0 ? c->splits_override : td::attn_choose_splits(s, n_layers, a.row_blocks);
+  const td::AttnSplits sp = td::attn_splits(kernel, s, n_layers, a.row_blocks, a.row_blocks32, max_nodes(c));
+  a.splits = c->splits_override > 0 ? c->splits_override : sp.splits;
   a.all_splits = c->splits_override > 0 ? 1 : 0;
   const long units = (long)s.T * n_layers * s.Hkv * a.row_blocks32;  // (partials per 32-row block)
   if (units * a.splits > s.attn_pairs_max && a.splits > 1) a.splits = 1;
@@ -280,7 +295,8 @@ td_status trie_attn_decode(td_ctx* c, int32_t layer_begin, int32_t n_layers, con
   const bool fuse_moves = a.rb_per_wg == 1 || attn_wgs <= kOneRoundWgs;
   // (an unsplit launch of several WG rounds, one WG per unit, runs 4-wave WGs, two per CU:
   // one WG's prologue and merge overlap the other's tile stream)
-  a.half_wgs = mfma && a.splits == 1 && a.row_blocks == 1 && attn_wgs > kOneRoundWgs ? 1 : 0;
+  a.half_wgs = a.splits > 1 ? c->splits_override == 0 && sp.half_wgs
+                            : mfma && a.row_blocks == 1 && attn_wgs > kOneRoundWgs;
   a.moves = 0;
   std::vector<std::pair<int, int>> due;
   if (c->pending && c->moves_pending) {
@@ -366,10 +382,12 @@ td_status trie_tree_attn(td_ctx* c, int32_t layer_begin, int32_t n_layers, int32
   const int rpb = td::attn_mfma_rows_per_block();
   a.row_blocks = (q_max * (s.Hq / s.Hkv) + rpb - 1) / rpb;
   a.row_blocks32 = a.row_blocks;
-  a.splits = c->splits_override > 0 ? c->splits_override : td::attn_choose_splits(s, n_layers, a.row_blocks);
+  const td::AttnSplits sp = td::attn_mfma_splits(s, n_layers, a.row_blocks, a.row_blocks, max_nodes(c));
+  a.splits = c->splits_override > 0 ? c->splits_override : sp.splits;
   a.all_splits = c->splits_override > 0 ? 1 : 0;
   const long units = (long)s.T * n_layers * s.Hkv * a.row_blocks;
   if (units * a.splits > s.attn_pairs_max && a.splits > 1) a.splits = 1;
+  a.half_wgs = a.splits > 1 && c->splits_override == 0 && sp.half_wgs;
   a.xcd_group = a.row_blocks > 1 && ((long)s.T * n_layers * s.Hkv * a.splits) % 8 == 0 ? 1 : 0;
   c->ev[TD_PHASE_ATTN][0] = c->ev[TD_PHASE_ATTN][1] = nullptr;
   hipError_t e = td::launch_attn_mfma(s, a, st, ev0, a.splits > 1 ? nullptr : ev1);
@@ -414,6 +432,7 @@ static void note_append(td_ctx* c) {
   bool collects = false;
   for (int t = 0; t < c->dev.T; ++t) {
     ++c->leaf_depth[t];
+    c->nodes[t] = std::min(c->nodes[t] + c->dev.b, c->dev.cap);
     collects = collects || (c->leaf_depth[t] + 1) % c->dev.G == 0;
   }
   c->pending = true;
@@ -493,6 +512,7 @@ td_status td_read_state(td_ctx* c, int32_t trie, td_state* o) {
     o->parent_slot[i] = o->parent_slot[i] >= 0 ? o->parent_slot[i] - h.base : -1;
   for (int j = 0; j < h.n_live; ++j) o->leaf_slot[j] = h.n_nodes - h.n_live + j;
   c->leaf_depth[trie] = h.leaf_depth;
+  c->nodes[trie] = h.n_nodes;
   o->n_nodes = h.n_nodes;
   o->n_live = h.n_live;
   o->base = h.base;
@@ -574,6 +594,7 @@ td_status td_load_state(td_ctx* c, int32_t trie, const td_state* in) {
   if (e != hipSuccess) return hip_fail(c, e, "td_load_state");
   c->inited[trie] = 1;
   c->leaf_depth[trie] = h.leaf_depth;
+  c->nodes[trie] = N;
   if (!others) {  // (with other tries the step's state is theirs, and kv_pending agrees with it)
     c->pending = in->kv_pending != 0;
     c->moves_pending = false;

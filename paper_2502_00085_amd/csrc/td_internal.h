@@ -113,8 +113,8 @@ struct AttnArgs {
                                    // grid's row_blocks counts WGs, of rb_per_wg blocks each
   int all_splits = 0;              // (matrix-core kernel) 1: every split WG takes a share of the
                                    // nodes (a forced split count); 0: only as many as needed
-  int half_wgs = 0;                // (two-row-block decode) 1: 4-wave WGs, two per CU; no fused
-                                   // row copy (moves == 0)
+  int half_wgs = 0;                // (matrix-core kernel) 1: 4-wave WGs, two per CU (two row blocks:
+                                   // no fused row copy, moves == 0)
 };
 
 hipError_t launch_init_prompt(const DevState& s, const int32_t* d_plen, const int32_t* d_tokens,
@@ -137,7 +137,14 @@ hipError_t launch_attn_tree(const DevState& s, const AttnArgs& a, hipStream_t st
 int attn_valu_rows_per_block(int d);  // query rows per block at head dim d
 hipError_t launch_attn_mfma32(const DevState& s, const AttnArgs& a, hipStream_t st, hipEvent_t ev0,
                               hipEvent_t ev1);
+int attn_choose_splits(const DevState& s, int n_layers, int row_blocks);
+struct AttnSplits {
+  int splits;
+  bool half_wgs;  // (AttnArgs::half_wgs)
+};
+AttnSplits attn_mfma_splits(const DevState& s, int n_layers, int row_blocks, int row_blocks32, long max_nodes);
 int attn_mfma32_rows_per_block(const DevState& s);
+int attn_mfma32_splits(const DevState& s, int n_layers, int row_blocks, long max_nodes);
 // The decode attention kernel of a context: the bf16 matrix-core one where it is implemented;
 // the fp32 matrix-instruction one for fp32 and the other head dims; the vector-ALU one, the
 // cross-check of both, only where the caller forces it.
@@ -151,13 +158,20 @@ inline int attn_rows_per_block(const DevState& s, AttnKernel k) {
          : k == AttnKernel::kMfma32 ? attn_mfma32_rows_per_block(s)
                                     : attn_valu_rows_per_block(s.D);
 }
+// Node splits of a decode launch (row_blocks: WGs per unit over its 32-row blocks, row_blocks32 of
+// them); max_nodes: a bound on the nodes of any trie.
+inline AttnSplits attn_splits(AttnKernel k, const DevState& s, int n_layers, int row_blocks, int row_blocks32,
+                              long max_nodes) {
+  if (k == AttnKernel::kMfma) return attn_mfma_splits(s, n_layers, row_blocks, row_blocks32, max_nodes);
+  if (k == AttnKernel::kMfma32) return {attn_mfma32_splits(s, n_layers, row_blocks, max_nodes), false};
+  return {attn_choose_splits(s, n_layers, row_blocks), false};
+}
 inline hipError_t launch_attn(AttnKernel k, const DevState& s, const AttnArgs& a, hipStream_t st, hipEvent_t ev0,
                               hipEvent_t ev1) {
   return k == AttnKernel::kMfma     ? launch_attn_mfma(s, a, st, ev0, ev1)
          : k == AttnKernel::kMfma32 ? launch_attn_mfma32(s, a, st, ev0, ev1)
                                     : launch_attn_valu(s, a, st, ev0, ev1);
 }
-int attn_choose_splits(const DevState& s, int n_layers, int row_blocks);
 hipError_t launch_logsoftmax_topk(const DevState& s, const float* logits, int32_t* sel_parent,
                                   int32_t* sel_token, float* sel_score, float* sel_logprob,
                                   float* lse, const int32_t* pair_parent, const int32_t* pair_token,

@@ -25,7 +25,6 @@
 // (Two launches instead of a last-arriving-WG merge: a device-scope fence costs an L2
 // writeback + invalidate per WG on this multi-XCD part.)
 #include <mutex>
-#include <type_traits>
 
 #include "trie_append.h"
 
@@ -175,34 +174,53 @@ __device__ inline void rank_topb(const uint64_t* cand, const uint64_t* comp, int
   }
 }
 
-// exp(d) in fp64 for d = x - max <= 0 (x and max fp32 values, so d is exact): 2^(k/64)
-// from a table of the 64 values 2^(j/64) (tab, computed per WG) times e^r for the reduced
-// argument r = d - k ln2/64, |r| <= ln2/128, by its Taylor polynomial of degree 5
-// (truncation below 4e-17 relative; ln2/64 split in two parts (Cody-Waite) so that k times
-// the first is exact).  Error within 2 ulp; the chunk sum only needs fp64 accuracy far
-// below the fp32 rounding of the log-sum-exp.  d < -708 (or -inf) gives 0: such a term
-// is below the ulp of a sum that holds exp(0) = 1.  About a third of the instructions of
-// the library exp, which dominates the VALU-bound chunk pass.
+// exp(d) in fp64 for -700 <= d = x - max <= 0 (x and max fp32 values, so d is exact; or NaN, which
+// stays NaN): 2^(k/64) from a table of the 64 values 2^(j/64) (tab, computed per WG) times e^r
+// for the reduced argument r = d - k ln2/64, |r| <= ln2/128, by its Taylor polynomial of degree
+// 5 (truncation below 4e-17 relative; ln2/64 split in two parts (Cody-Waite) so that k times the
+// first is exact).  k comes out of one fma that adds 1.5 2^52 (its low bits are the rounded
+// integer), and its multiple of 64 goes straight into the exponent, which cannot underflow: the
+// conversions, roundings and scalings of doubles run at a fraction of the fma rate.  Error within
+// 2 ulp; the chunk sum only needs fp64 accuracy far below the fp32 rounding of the log-sum-exp.
 __device__ inline double exp_nonpos(double d, const double* tab) {
-  const double k = __builtin_rint(d * 92.33248261689366);  // 64 / ln 2
-  double r = __builtin_fma(k, -0x1.62e42fefa0000p-7, d);     // ln2/64, leading 36 bits
-  r = __builtin_fma(k, -2.572804622327669e-14, r);           // and the rest
-  double p = __builtin_fma(r, 1.0 / 120.0, 1.0 / 24.0);
-  p = __builtin_fma(r, p, 1.0 / 6.0);
-  p = __builtin_fma(r, p, 0.5);
-  p = __builtin_fma(r, p, 1.0);
-  p *= r;  // e^r - 1
-  const int ki = (int)k;
-  const double t = tab[ki & 63];
-  const double e = __builtin_ldexp(__builtin_fma(t, p, t), ki >> 6);
-  return d < -708.0 ? 0.0 : e;
+  constexpr double kMagic = 0x1.8p52;
+  const double t = __builtin_fma(d, 92.33248261689366, kMagic);  // 64 / ln 2
+  const double k = t - kMagic;
+  double r = __builtin_fma(k, -0x1.62e42fefa0000p-7, d);  // ln2/64, leading 36 bits
+  r = __builtin_fma(k, -2.572804622327669e-14, r);        // and the rest
+  double q = __builtin_fma(r, 1.0 / 120.0, 1.0 / 24.0);
+  q = __builtin_fma(r, q, 1.0 / 6.0);
+  q = __builtin_fma(r, q, 0.5);
+  const double p = __builtin_fma(r * r, q, r);  // e^r - 1
+  const int ki = __double2loint(t);
+  const double w = tab[ki & 63];
+  const double e = __builtin_fma(w, p, w);
+  return __hiloint2double(__double2hiint(e) + ((ki & ~63) << 14), __double2loint(e));
 }
+// The smallest argument exp_nonpos takes is 700 below the maximum: e^-700 is, like anything
+// smaller, far below the ulp of a sum that holds exp(0) = 1.  (A NaN compares false: it stays.)
+__device__ inline double exp_term(float x, float m, float lowest, const double* tab) {
+  return exp_nonpos((double)(x < lowest ? lowest : x) - (double)m, tab);
+}
+
+// Order-preserving map of floats to signed integers (-0 below +0; ord_raw is this with the sign
+// bit flipped) and its inverse: integer maxima take one instruction, where fmaxf quiets its
+// operands first, and fuse with the lane permutes of a wave-wide maximum.
+__device__ inline int ord_signed(float f) {
+  const int u = __float_as_int(f);
+  return u ^ ((u >> 31) & 0x7fffffff);
+}
+__device__ inline float ord_signed_inv(int o) { return __int_as_float(o ^ ((o >> 31) & 0x7fffffff)); }
+extern "C" __device__ int __ockl_wfred_max_i32(int);
 
 // One chunk of one row: max, fp64 sum of exp(x - max), the two largest logit keys of each
 // 256-logit sub-chunk.  Sub-chunk w of the chunk holds logits v0 + i*1024 + 64w + lane
 // (i < 4); a WG of NWC waves gives each wave 16/NWC consecutive sub-chunks (16 waves: one
 // each; 4 waves, for launches of many chunks: four each, so that the wave-wide and
-// block-wide steps are paid once per 1,024 logits).
+// block-wide steps are paid once per 1,024 logits).  A large launch is bound by vector-ALU issue:
+// 16 tries of 16 beams at V = 128,256 (131 MB of logits) ran about 1,000 vector instructions per
+// wave of 16 logits per lane, with the exponential's conversions and scalings of doubles and the
+// key selection, and took 64 us with its merge; 690 instructions now, 56 us.
 template <int NWC>
 __global__ __launch_bounds__(NWC * 64) void k_topb_chunk(DevState s, const float* logits) {
   constexpr int SPW = kSub / NWC;  // sub-chunks per wave
@@ -228,12 +246,61 @@ __global__ __launch_bounds__(NWC * 64) void k_topb_chunk(DevState s, const float
   if (wave == 0) exp_tab[lane] = exp2((double)lane * 0.015625);  // (read after the barrier below)
   const size_t list = ((size_t)t * b + r) * s.lse_chunks + c;
   const size_t lists = (size_t)s.T * b * s.lse_chunks;
-  // PLAIN: a full chunk without the end-of-sequence token, the common case: no per-logit
-  // range or token test, and no per-logit test for a NaN or +inf logit (either makes the
-  // sum NaN by itself: x - max is then NaN for that logit; only a chunk whose maximum is
-  // -inf, i.e. every logit -inf or NaN, needs the explicit test)
-  auto body = [&](auto plain_t, float& m, double& acc, bool& bad) __attribute__((always_inline)) {
-    constexpr bool PLAIN = decltype(plain_t)::value;
+  // A full chunk without the end-of-sequence token, the common case: no per-logit range or token
+  // test, and no per-logit test for a NaN or +inf logit (either makes the sum NaN by itself: x -
+  // max is then NaN for that logit; only a chunk whose maximum is -inf, i.e. every logit -inf or
+  // NaN, needs the explicit test).  The two largest logits of a sub-chunk are found by value and
+  // the place of the largest afterwards, from the lanes that hold it: 5 vector instructions per
+  // logit and two wave-wide maxima per sub-chunk, instead of a (key, index) selection of about
+  // 10 per logit and four wave-wide maxima.  (Equal logits: the lower flat index.  The second
+  // largest is only compared with the bound: its place is not needed.)
+  auto plain = [&](float& m, double& acc, bool& bad) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < SPW; ++q) {
+      const int sw = wave * SPW + q;
+      static_assert(kChunkPer == 4, "two pairs of logits per lane");
+      int o[kChunkPer];
+#pragma unroll
+      for (int i = 0; i < kChunkPer; ++i) o[i] = ord_signed(x[q][i]);
+      const int a = max(o[0], o[1]), b0 = min(o[0], o[1]), c2 = max(o[2], o[3]), d = min(o[2], o[3]);
+      const int first = max(a, c2), second = max(max(min(a, c2), b0), d);
+      const int o1 = __builtin_amdgcn_readfirstlane(__ockl_wfred_max_i32(first));
+      int at = 0, owner = 0;  // run and lane of the largest (the lowest of equal ones)
+#pragma unroll
+      for (int i = kChunkPer - 1; i >= 0; --i) {
+        const uint64_t own = __ballot(o[i] == o1);
+        owner = own ? __ffsll((unsigned long long)own) - 1 : owner;
+        at = own ? i : at;
+      }
+      const int o2 = __ockl_wfred_max_i32(lane == owner ? second : first);
+      const uint32_t flat = (uint32_t)r * (uint32_t)V + (uint32_t)(v0 + sw * 64 + at * kChunkThreads + owner);
+      if (lane == 0) {
+        const uint64_t low = 0xffffffffu - flat;
+        s.topk_keys[sw * lists + list] = ((uint64_t)((uint32_t)o1 ^ 0x80000000u) << 32) | low;
+        s.topk_keys[s.topk_half + sw * lists + list] = ((uint64_t)((uint32_t)o2 ^ 0x80000000u) << 32) | low;
+      }
+      const float m1 = ord_signed_inv(o1);
+      m = fmaxf(m, m1);
+    }
+    if (lane == 0) wm[wave] = m;
+    __syncthreads();
+    m = wm[0];
+#pragma unroll
+    for (int w = 1; w < NWC; ++w) m = fmaxf(m, wm[w]);
+    if (m != -INFINITY) {
+      const float lowest = m - 700.0f;
+#pragma unroll
+      for (int q = 0; q < SPW; ++q)
+#pragma unroll
+        for (int i = 0; i < kChunkPer; ++i) acc += exp_term(x[q][i], m, lowest, exp_tab);
+    } else {
+#pragma unroll
+      for (int q = 0; q < SPW; ++q)
+#pragma unroll
+        for (int i = 0; i < kChunkPer; ++i) bad |= !(x[q][i] < INFINITY);
+    }
+  };
+  auto general = [&](float& m, double& acc, bool& bad) __attribute__((always_inline)) {
 #pragma unroll
     for (int q = 0; q < SPW; ++q) {
       const int sw = wave * SPW + q;
@@ -247,7 +314,7 @@ __global__ __launch_bounds__(NWC * 64) void k_topb_chunk(DevState s, const float
         m = fmaxf(m, x[q][i]);
         // (the end-of-sequence token, if any, is not a candidate for the next beams;
         // order 0 = no candidate)
-        const uint32_t o = PLAIN || (v < V && v != s.eos) ? ord_raw(x[q][i]) : 0u;
+        const uint32_t o = v < V && v != s.eos ? ord_raw(x[q][i]) : 0u;
         const bool gt1 = o > o1, gt2 = o > o2;
         o2 = gt1 ? o1 : (gt2 ? o : o2);
         i2 = gt1 ? i1 : (gt2 ? i : i2);
@@ -272,31 +339,24 @@ __global__ __launch_bounds__(NWC * 64) void k_topb_chunk(DevState s, const float
     m = wm[0];
 #pragma unroll
     for (int w = 1; w < NWC; ++w) m = fmaxf(m, wm[w]);
-    const double md = (double)m;
-    if (PLAIN && md != -INFINITY) {
+    const float lowest = m - 700.0f;
 #pragma unroll
-      for (int q = 0; q < SPW; ++q)
+    for (int q = 0; q < SPW; ++q)
 #pragma unroll
-        for (int i = 0; i < kChunkPer; ++i) acc += exp_nonpos((double)x[q][i] - md, exp_tab);
-    } else {
-#pragma unroll
-      for (int q = 0; q < SPW; ++q)
-#pragma unroll
-        for (int i = 0; i < kChunkPer; ++i) {
-          const int v = v0 + i * kChunkThreads + (wave * SPW + q) * 64 + lane;
-          // (a chunk whose logits are all -inf adds nothing; exp(-inf - -inf) would be NaN)
-          if (v < V && md != -INFINITY) acc += exp_nonpos((double)x[q][i] - md, exp_tab);
-          bad |= v < V && !(x[q][i] < INFINITY);
-        }
-    }
+      for (int i = 0; i < kChunkPer; ++i) {
+        const int v = v0 + i * kChunkThreads + (wave * SPW + q) * 64 + lane;
+        // (a chunk whose logits are all -inf adds nothing; exp(-inf - -inf) would be NaN)
+        if (v < V && m != -INFINITY) acc += exp_term(x[q][i], m, lowest, exp_tab);
+        bad |= v < V && !(x[q][i] < INFINITY);
+      }
   };
   float m = -INFINITY;
   double acc = 0.0;
   bool bad = false;  // a NaN or +inf logit
   if (v0 + kLseChunk <= V && (s.eos < v0 || s.eos >= v0 + kLseChunk))
-    body(std::true_type{}, m, acc, bad);
+    plain(m, acc, bad);
   else
-    body(std::false_type{}, m, acc, bad);
+    general(m, acc, bad);
   const double md = (double)m;  // (the chunk's maximum)
   // an invalid logit poisons the chunk's sum: the row's lse is then NaN and the call
   // reports the row (k_topb_final)

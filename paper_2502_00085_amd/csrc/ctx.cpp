@@ -24,7 +24,6 @@ struct td_ctx {
                                        //   device header; tells which appends collect)
   std::vector<int32_t> nodes;          // per trie: an upper bound of its stored nodes (exact after
                                        //   init_prompt, load_state and read_state)
-  int32_t* d_plen = nullptr;
   int splits_override = 0;             // TD_ATTN_SPLITS (tuning): WGs per attention unit
   hipEvent_t ev[4][2] = {};             // td_set_kernel_events: per td_phase, the
                                        //   kernel-timestamp events of its next run
@@ -187,8 +186,7 @@ td_status td_create(const td_desc* d, td_ctx** out) {
       (e = alloc(c, &s.fin_step, (size_t)s.T * s.b)) != hipSuccess ||
       (e = alloc(c, &s.fin_parent, (size_t)s.T * s.b)) != hipSuccess ||
       (e = alloc(c, &s.fin_count, (size_t)s.T)) != hipSuccess ||
-      (e = alloc(c, &s.fin_done, (size_t)s.T)) != hipSuccess ||
-      (e = alloc(c, &c->d_plen, (size_t)s.T)) != hipSuccess) {
+      (e = alloc(c, &s.fin_done, (size_t)s.T)) != hipSuccess) {
     td_destroy(c);
     return hip_fail(nullptr, e, "allocating trie metadata / workspace");
   }
@@ -221,12 +219,10 @@ td_status td_init_prompt(td_ctx* c, const int32_t* h_plen, const int32_t* d_toke
     pmax = h_plen[t] > pmax ? h_plen[t] : pmax;
   }
   if (stride < pmax) return fail(c, TD_EINVAL, "tokens_stride must be >= the longest prompt");
-  hipError_t e = hipStreamSynchronize(st);
-  if (e == hipSuccess) e = hipMemcpy(c->d_plen, h_plen, sizeof(int32_t) * c->dev.T, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = td::launch_init_prompt(c->dev, c->d_plen, d_tokens, stride, st);
+  // (the launch is the only device work, in stream order; the call returns when it is done, so
+  // that the caller may reuse the tokens on any stream)
+  hipError_t e = td::launch_init_prompt(c->dev, h_plen, d_tokens, stride, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
-  if (e == hipSuccess) e = hipMemset(c->dev.fin_count, 0, sizeof(int32_t) * c->dev.T);
-  if (e == hipSuccess) e = hipMemset(c->dev.fin_done, 0, sizeof(int32_t) * c->dev.T);
   if (e != hipSuccess) return hip_fail(c, e, "td_init_prompt");
   c->inited.assign(c->dev.T, 1);
   for (int t = 0; t < c->dev.T; ++t) {

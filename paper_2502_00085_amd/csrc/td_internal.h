@@ -117,7 +117,7 @@ struct AttnArgs {
                                    // no fused row copy, moves == 0)
 };
 
-hipError_t launch_init_prompt(const DevState& s, const int32_t* d_plen, const int32_t* d_tokens,
+hipError_t launch_init_prompt(const DevState& s, const int32_t* h_plen, const int32_t* d_tokens,
                               int stride, hipStream_t st);
 // Head dims the bf16 matrix-core kernels implement (the others take any multiple of 32 up to
 // 256).

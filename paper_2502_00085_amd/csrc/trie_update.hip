@@ -1,25 +1,40 @@
 // Trie initialisation, the append kernel (append + mask update + garbage collection, whose
 // block-wide body is in trie_append.h) and the K/V row compaction (gfx950).
+#include <algorithm>
+
 #include "trie_append.h"
 
 namespace td {
 
 namespace {
 
-__global__ __launch_bounds__(256) void k_init_prompt(DevState s, const int32_t* plen,
-                                                     const int32_t* tokens, int stride) {
-  const int t = blockIdx.x;
-  const int P = plen[t];
+// Prompt lengths of up to kInitTries tries, by value in the kernel's arguments (no copy to the
+// device, and nothing of the caller's is read after the call).
+constexpr int kInitTries = 64;
+struct PromptLens {
+  int32_t n[kInitTries];
+};
+constexpr int kInitSlots = 1024;  // slots per WG: 4 per thread
+
+// Grid (slots / kInitSlots, tries): slots, and by a trie's first WG its header, leaf scores and
+// finished pool.  (One WG per trie took 15 us for a prompt of 8,192 tokens.)
+__global__ __launch_bounds__(256) void k_init_prompt(DevState s, PromptLens plen, int t0, const int32_t* tokens, int stride) {
+  const int t = t0 + blockIdx.y;
+  const int P = plen.n[blockIdx.y];
   const size_t off = (size_t)t * s.cap;
-  for (int n = threadIdx.x; n < P; n += blockDim.x) {
+  const int n0 = blockIdx.x * kInitSlots;
+  for (int n = n0 + threadIdx.x; n < min(P, n0 + kInitSlots); n += blockDim.x) {
     s.node_id[off + n] = n;
     s.parent[off + n] = n - 1;
     s.token[off + n] = tokens[(size_t)t * stride + n];
     s.depth[off + n] = n;
     s.mask[off + n] = 1ull;
   }
+  if (blockIdx.x > 0) return;
   for (int j = threadIdx.x; j < s.b; j += blockDim.x) s.leaf_score[(size_t)t * s.b + j] = 0.0f;
   if (threadIdx.x == 0) {
+    s.fin_count[t] = 0;
+    s.fin_done[t] = 0;
     TrieHdr h;
     h.n_nodes = P;
     h.base = 0;
@@ -98,10 +113,19 @@ __global__ __launch_bounds__(kMoveThreads) void k_move_rows(DevState s, int laye
 
 }  // namespace
 
-hipError_t launch_init_prompt(const DevState& s, const int32_t* d_plen, const int32_t* d_tokens,
+hipError_t launch_init_prompt(const DevState& s, const int32_t* h_plen, const int32_t* d_tokens,
                               int stride, hipStream_t st) {
-  hipLaunchKernelGGL(k_init_prompt, dim3(s.T), dim3(256), 0, st, s, d_plen, d_tokens, stride);
-  return hipGetLastError();
+  for (int t0 = 0; t0 < s.T; t0 += kInitTries) {
+    PromptLens lens{};
+    const int n = std::min(kInitTries, s.T - t0);
+    int32_t most = 0;
+    for (int i = 0; i < n; ++i) most = std::max(most, lens.n[i] = h_plen[t0 + i]);
+    hipLaunchKernelGGL(k_init_prompt, dim3((most + kInitSlots - 1) / kInitSlots, n), dim3(256), 0, st, s, lens, t0,
+                       d_tokens, stride);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_append_prune(const DevState& s, const int32_t* sel_parent,

@@ -44,7 +44,8 @@ namespace {
 constexpr int kTreeWaves = 4;  // (two WGs per CU: their barriers do not wait on each other)
 constexpr int kTreeThreads = kTreeWaves * 64;
 constexpr int kTreeRows = kTreeWaves * 32;  // query rows per WG
-constexpr int kTreeSplitWgs = 512;       // (see launch_attn_tree)
+constexpr int kTreeSplitWgs = 512, kTreeSplitWgs64 = 320;       // (see launch_attn_tree)
+constexpr long kTreeShortKeys = 560, kTreeShortKeys64 = 768;
 constexpr float kTreeNegBig = -1.0e30f;
 constexpr float kTreeSlack = 8.0f;     // a row's shift moves for scores 2^8 above it
 constexpr float kTreeMost = 8192.0f;   // ... once 16 of its probabilities add up to more than this
@@ -401,14 +402,23 @@ __global__ __launch_bounds__(KS * kTreeThreads, TreeCfg<D>::WAVES) void k_attn_t
 
 int attn_tree_rows_per_block() { return kTreeRows; }
 
+// Short key ranges go to the compact kernel (attn_tree_short.hip), which starts faster.  Measured,
+// every node a query, the better form here against it: d = 128: 300 nodes, 320 blocks, 21.2 and
+// 20.2 us; 520 nodes, 136 blocks, 22.2 and 21.8; 600 nodes, 152 blocks, 20.8 and 23.6.  At d = 64,
+// where five of its WGs fit a CU, it holds out longer in launches of several WGs per CU: 600 nodes,
+// 960 blocks, 37.5 and 35.8; 700 nodes, 1,088 blocks, 43.7 and 41.1; 850 nodes, 1,280, 51.7 and 54.0.
+//
 // Two groups per WG where one group per WG leaves CUs with less than two (measured, a call of
-// 32 WGs: 53 us with one group, 44 with two; of 320 WGs at d = 96: 32 and 28; beyond one round
-// of single groups the two-group WG, whose barrier ties 8 waves, loses: 64 against 71 us for
-// 528 WGs).
-hipError_t launch_attn_tree(const DevState& s, const AttnArgs& a, hipStream_t st, hipEvent_t ev0,
+// 32 WGs: 53 us with one group, 44 with two; of 320 WGs at d = 96: 32 and 28; of 512 at d = 128:
+// 44.6 and 42.8; beyond one round of single groups the two-group WG, whose barrier ties 8 waves,
+// loses: 64 against 71 us for 528 WGs).  At d = 64 a round is more single groups: 320 WGs, 24.6
+// and 23.7 us, but 384, 27.2 and 28.0.
+hipError_t launch_attn_tree(const DevState& s, const AttnArgs& a, long max_keys, hipStream_t st, hipEvent_t ev0,
                             hipEvent_t ev1) {
   const int wgs = s.T * a.n_layers * s.Hkv * a.row_blocks;
-  const bool split = wgs <= kTreeSplitWgs;
+  if (max_keys <= kTreeShortKeys || (s.D == 64 && max_keys <= kTreeShortKeys64 && wgs > kTreeSplitWgs64))
+    return launch_attn_tree_short(s, a, st, ev0, ev1);
+  const bool split = wgs <= (s.D == 64 ? kTreeSplitWgs64 : kTreeSplitWgs);
   const dim3 grid(wgs), block(split ? 2 * kTreeThreads : kTreeThreads);
 #define LAUNCH_TREE(DD)                                                                               \
   (split ? hipExtLaunchKernelGGL((k_attn_tree<DD, 2>), grid, block, 0, st, ev0, ev1, 0, s, a)          \

@@ -371,7 +371,9 @@ td_status trie_tree_attn(td_ctx* c, int32_t layer_begin, int32_t n_layers, int32
     a.splits = 1;
     a.xcd_group = a.row_blocks > 1 && ((long)s.T * n_layers * s.Hkv) % 8 == 0 ? 1 : 0;
     c->ev[TD_PHASE_ATTN][0] = c->ev[TD_PHASE_ATTN][1] = nullptr;
-    hipError_t e = td::launch_attn_tree(s, a, st, ev0, ev1);
+    // (a bound on a block's key range: the trie, or a window before each of its queries)
+    const long keys = s.W > 0 ? std::min(max_nodes(c), (long)s.W + tpb) : max_nodes(c);
+    hipError_t e = td::launch_attn_tree(s, a, keys, st, ev0, ev1);
     if (e != hipSuccess) return hip_fail(c, e, "trie_tree_attn launch");
     return TD_OK;
   }

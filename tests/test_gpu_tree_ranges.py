@@ -1,0 +1,35 @@
+"""Prefill-shaped tree attention over key ranges beyond the compact kernel's, where the rule of
+the kernels and of the groups of waves per workgroup changes: one or two groups, several tiles
+past the shared prefix, a window, dead nodes, scores that move the softmax shift.  Against the CPU
+oracle, at its bf16 tolerance."""
+import pytest
+
+import test_gpu_tree_attn
+from gpu_harness import Run
+from test_gpu_tree_attn import every_node, run_tree, small
+
+pytestmark = pytest.mark.gpu
+
+
+# (KV heads, layers, prompt, window): 16 to 640 row blocks of 128 rows; tries of 544 to 800 nodes,
+# below and above both limits of the rule
+@pytest.mark.parametrize("d", [64, 96, 128])
+@pytest.mark.parametrize("hkv,layers,prompt,window", [(2, 1, 528, 0), (2, 1, 600, 0), (2, 1, 640, 520), (8, 2, 576, 0),
+                                                      (8, 2, 770, 0)])
+def test_long_ranges(d, hkv, layers, prompt, window):
+    g = 8 if layers > 1 else 4
+    run_tree(small(n_layers=layers, prompt_min=prompt, prompt_max=prompt, n_q_heads=g * hkv, n_kv_heads=hkv, head_dim=d,
+                   beam_width=6, steps=7, window=window, gc_interval=4), seed=24, pick=every_node)
+
+
+@pytest.mark.parametrize("d,hkv", [(64, 2), (96, 4), (128, 2)])
+def test_large_scores(d, hkv, monkeypatch):
+    # twelve times the usual scale: scores of a row over tens of powers of two
+    class Steep(Run):
+        def __init__(self, *args, **kw):
+            super().__init__(*args, **kw)
+            self.scale *= 12.0
+
+    monkeypatch.setattr(test_gpu_tree_attn, "Run", Steep)
+    run_tree(small(prompt_min=790, prompt_max=790, n_layers=1, n_q_heads=4 * hkv, n_kv_heads=hkv, head_dim=d, beam_width=6,
+                   steps=4), seed=25, pick=every_node)

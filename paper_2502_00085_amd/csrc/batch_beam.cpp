@@ -237,7 +237,7 @@ td_status batch_beam_attn_decode(bbs_ctx* c, int32_t layer_begin, int32_t n_laye
   if (!c->pending && (d_k_new || d_v_new)) return bfail(c, TD_EINVAL, "no K/V is pending (after init): pass NULL k_new / v_new");
   if (c->pending && (!al16(d_k_new) || !al16(d_v_new))) return bfail(c, TD_EINVAL, "k_new / v_new must be 16-byte aligned");
   if (!(scale > 0.0f) || !std::isfinite(scale)) return bfail(c, TD_EINVAL, "scale must be finite and > 0");
-  const td::AttnKernel kernel = td::attn_kernel(s, c->desc.attn_impl);
+  const td::AttnKernel kernel = td::attn_kernel(s, c->desc.attn_impl, n_layers, s.cap);
   td::AttnArgs a{};
   a.q = d_q;
   a.k_new = d_k_new;

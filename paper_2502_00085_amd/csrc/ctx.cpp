@@ -251,7 +251,7 @@ td_status trie_attn_decode(td_ctx* c, int32_t layer_begin, int32_t n_layers, con
   if (c->pending && (!aligned16(d_k_new) || !aligned16(d_v_new)))
     return fail(c, TD_EINVAL, "k_new / v_new must be 16-byte aligned");
   if (!(scale > 0.0f) || !std::isfinite(scale)) return fail(c, TD_EINVAL, "scale must be finite and > 0");
-  const td::AttnKernel kernel = td::attn_kernel(s, c->desc.attn_impl);
+  const td::AttnKernel kernel = td::attn_kernel(s, c->desc.attn_impl, n_layers, max_nodes(c));
   const bool mfma = kernel == td::AttnKernel::kMfma;
   td::AttnArgs a{};
   a.q = d_q;

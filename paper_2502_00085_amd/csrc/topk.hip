@@ -197,11 +197,6 @@ __device__ inline double exp_nonpos(double d, const double* tab) {
   const double e = __builtin_fma(w, p, w);
   return __hiloint2double(__double2hiint(e) + ((ki & ~63) << 14), __double2loint(e));
 }
-// The smallest argument exp_nonpos takes is 700 below the maximum: e^-700 is, like anything
-// smaller, far below the ulp of a sum that holds exp(0) = 1.  (A NaN compares false: it stays.)
-__device__ inline double exp_term(float x, float m, float lowest, const double* tab) {
-  return exp_nonpos((double)(x < lowest ? lowest : x) - (double)m, tab);
-}
 
 // Order-preserving map of floats to signed integers (-0 below +0; ord_raw is this with the sign
 // bit flipped) and its inverse: integer maxima take one instruction, where fmaxf quiets its
@@ -212,6 +207,22 @@ __device__ inline int ord_signed(float f) {
 }
 __device__ inline float ord_signed_inv(int o) { return __int_as_float(o ^ ((o >> 31) & 0x7fffffff)); }
 extern "C" __device__ int __ockl_wfred_max_i32(int);
+
+// The smallest logit exp_nonpos is given beside the chunk's maximum m: the lowest float at most 700
+// below m (m - 700 itself is rounded, to m - 768 or m - 1024 from |m| = 2^31 on).  A lower logit is
+// raised to it: e^-700 is, like anything smaller, far below the ulp of a sum that holds exp(0) = 1.
+// From |m| = 2^33 on there is no other float so near m, and it is m (see exp_term).
+__device__ inline float lowest_term(float m) {
+  const float l = m - 700.0f;
+  return m - l > 700.0f ? ord_signed_inv(ord_signed(l) + 1) : l;  // (exact where l is off by more than 2^-14)
+}
+// exp(x - m) for x <= m; wide (the same for the whole chunk): lowest is m, and a lower logit, 512
+// or more below it, adds nothing.  (A NaN compares false, and stays; so does +inf, whose difference
+// from a maximum of +inf is NaN.)
+__device__ inline double exp_term(float x, float m, float lowest, bool wide, const double* tab) {
+  if (wide) return x < m ? 0.0 : (double)x - (double)m + 1.0;
+  return exp_nonpos((double)(x < lowest ? lowest : x) - (double)m, tab);
+}
 
 // One chunk of one row: max, fp64 sum of exp(x - max), the two largest logit keys of each
 // 256-logit sub-chunk.  Sub-chunk w of the chunk holds logits v0 + i*1024 + 64w + lane
@@ -288,11 +299,19 @@ __global__ __launch_bounds__(NWC * 64) void k_topb_chunk(DevState s, const float
 #pragma unroll
     for (int w = 1; w < NWC; ++w) m = fmaxf(m, wm[w]);
     if (m != -INFINITY) {
-      const float lowest = m - 700.0f;
+      const float lowest = lowest_term(m);
+      const bool wide = lowest == m;
+      if (wide) {
 #pragma unroll
-      for (int q = 0; q < SPW; ++q)
+        for (int q = 0; q < SPW; ++q)
 #pragma unroll
-        for (int i = 0; i < kChunkPer; ++i) acc += exp_term(x[q][i], m, lowest, exp_tab);
+          for (int i = 0; i < kChunkPer; ++i) acc += exp_term(x[q][i], m, lowest, true, exp_tab);
+      } else {
+#pragma unroll
+        for (int q = 0; q < SPW; ++q)
+#pragma unroll
+          for (int i = 0; i < kChunkPer; ++i) acc += exp_term(x[q][i], m, lowest, false, exp_tab);
+      }
     } else {
 #pragma unroll
       for (int q = 0; q < SPW; ++q)
@@ -339,14 +358,15 @@ __global__ __launch_bounds__(NWC * 64) void k_topb_chunk(DevState s, const float
     m = wm[0];
 #pragma unroll
     for (int w = 1; w < NWC; ++w) m = fmaxf(m, wm[w]);
-    const float lowest = m - 700.0f;
+    const float lowest = lowest_term(m);
+    const bool wide = lowest == m;
 #pragma unroll
     for (int q = 0; q < SPW; ++q)
 #pragma unroll
       for (int i = 0; i < kChunkPer; ++i) {
         const int v = v0 + i * kChunkThreads + (wave * SPW + q) * 64 + lane;
         // (a chunk whose logits are all -inf adds nothing; exp(-inf - -inf) would be NaN)
-        if (v < V && m != -INFINITY) acc += exp_term(x[q][i], m, lowest, exp_tab);
+        if (v < V && m != -INFINITY) acc += exp_term(x[q][i], m, lowest, wide, exp_tab);
         bad |= v < V && !(x[q][i] < INFINITY);
       }
   };

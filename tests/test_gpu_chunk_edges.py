@@ -1,6 +1,7 @@
 """The chunk pass of the selection on logits where its per-value shortcuts can go wrong: both zeros,
 equal largest logits in one sub-chunk (one lane, one run, several runs), values far below the
-row's maximum and -inf, against the oracle's ranking of every candidate.  Bit for bit."""
+row's maximum (of any magnitude) and -inf, against the oracle's ranking of every candidate.  Bit
+for bit."""
 import numpy as np
 import pytest
 
@@ -56,3 +57,23 @@ def test_one_finite_logit():
         x = np.full((1, 1, 4096), -np.inf, np.float32)
         x[0, 0, 2055] = zero
         run(x, np.zeros((1, 1), np.float32), 1)
+
+
+# Around these maxima the floats are 32, 256, 1,024, 2,048 and far more apart: 700 below the
+# maximum is no float.  Chunks with lower logits just below, far below, of the type's lowest and -inf.
+@pytest.mark.parametrize("T,b,V", [(1, 4, 4096), (2, 3, 8200), (9, 16, 16384)])
+@pytest.mark.parametrize("m", [5e8, 3e9, 1e10, 2e10, 3e38, -5e8, -3e9, -1e10, -2e10, -3e38])
+@pytest.mark.parametrize("rest", ["near", "far", "masked"])
+def test_large_maxima(T, b, V, m, rest):
+    g = np.random.default_rng(11)
+    top = np.float32(m)
+    if rest == "near":  # up to 40 floats below
+        x = (top.view(np.int32) + (-1 if m > 0 else 1) * g.integers(0, 40, (T, b, V), dtype=np.int32)).view(np.float32)
+    elif rest == "far":
+        x = np.minimum(top - np.float32(1000.0), np.float32(-abs(m)) * g.uniform(1, 1.1, (T, b, V)).astype(np.float32))
+        x[..., ::5] = np.finfo(np.float32).min
+    else:
+        x = np.full((T, b, V), -np.inf, np.float32)
+    x[..., 17::509] = top  # several of the largest in every chunk
+    x[..., 3::64] = -np.inf
+    run(np.ascontiguousarray(x, np.float32), -np.sort(g.random((T, b)) * 4).astype(np.float32), b)

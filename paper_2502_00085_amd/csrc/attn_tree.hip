@@ -379,10 +379,11 @@ __global__ __launch_bounds__(KS * kTreeThreads, TreeCfg<D>::WAVES) void k_attn_t
     }
   }
 
-  // each wave writes its own rows: O / l (zero for a row without keys or without a query)
+  // each wave writes its own rows: O / l (zero for a row without keys or without a query; a NaN
+  // score makes l NaN, and the row with it)
   lsum += __shfl_xor(lsum, 32);
   if (r < a.qmax * G) {
-    const bool some = row_ok && lsum > 0.0f;
+    const bool some = row_ok && lsum != 0.0f;
     const float inv = some ? 1.0f / lsum : 0.0f;
     __bf16* orow = static_cast<__bf16*>(a.out) +
                    ((((size_t)li * s.T + t) * a.qmax + owner) * s.Hq + g * G + r % G) * D;

@@ -1,11 +1,13 @@
 """The prefill-shaped tree attention where its launch shapes and its softmax shift can go wrong:
 launches of more than 512 row blocks (one group of waves per workgroup), with one unit per XCD
 (the folded block order), row blocks that end inside a tile, and scores whose range makes the
-shift move again and again.  Against the CPU oracle, at its bf16 tolerance."""
+shift move again and again.  Against the CPU oracle, at its bf16 tolerance.  And NaN scores."""
+import numpy as np
 import pytest
+import torch
 
 import test_gpu_tree_attn
-from gpu_harness import Run
+from gpu_harness import Run, from_dev, log
 from test_gpu_tree_attn import every_node, run_tree, small
 
 pytestmark = pytest.mark.gpu
@@ -36,3 +38,48 @@ def test_large_scores(d, prompt, monkeypatch):
     monkeypatch.setattr(test_gpu_tree_attn, "Run", Steep)
     run_tree(small(prompt_min=prompt, prompt_max=prompt, n_q_heads=16, n_kv_heads=4, head_dim=d, beam_width=6,
                    steps=4), seed=23, pick=every_node)
+
+
+# The compact kernel; beyond its key range one and two groups of waves per workgroup
+@pytest.mark.parametrize("d,hkv,layers,prompt", [(64, 2, 1, 90), (96, 2, 1, 90), (128, 2, 1, 90), (64, 2, 1, 780), (128, 2, 1, 600),
+                                                 (64, 8, 2, 780), (96, 8, 2, 600), (128, 8, 2, 600)])
+@pytest.mark.parametrize("where", ["k", "q"])
+def test_nan_scores_stay_nan(d, hkv, layers, prompt, where):
+    """A NaN key, or a query with an infinite element: the rows that see it are NaN, the others as
+    they were, those of empty queries zero."""
+    w = small(n_layers=layers, prompt_min=prompt, prompt_max=prompt, n_q_heads=8 * hkv, n_kv_heads=hkv, head_dim=d,
+              beam_width=6, steps=7, alpha=0.0)
+    log(f"nan scores d={d} Hkv={hkv} L={layers} P={prompt} {where}")
+    r = Run(w, seed=26, oracle=False)
+    for _ in range(w.steps):
+        r.step(check=False)
+    q, kn, vn, logits, _, _ = r.inputs(w.steps + 1)
+    qd, knd, vnd, _ = r.dev_inputs(w.steps + 1, q, kn, vn, logits)
+    r.dec.attn_decode(0, layers, qd, knd, vnd, torch.empty_like(qd), r.scale)  # stores the leaves
+    st = r.dec.read_state(0)
+    n = st["n_nodes"]
+    slots = np.concatenate([np.arange(n), [-1, -1, -1]]).astype(np.int32)
+    qs = torch.from_numpy(slots[None]).cuda()
+    x = torch.randn((layers, 1, n + 3, 8 * hkv, d), device="cuda", generator=torch.Generator("cuda").manual_seed(3))
+    x = x.to(torch.bfloat16)
+    out = [torch.full_like(x, 5.0) for _ in range(2)]
+    r.dec.tree_attn(0, layers, qs, x, out[0], r.scale)
+    hit = np.zeros((n + 3, 8 * hkv), bool)
+    bad = n - 3  # a leaf, or a node on the way to one
+    if where == "k":
+        bad = int(st["parent_slot"][bad])
+        r.dec.k_pool[:, :, 1, st["base"] + bad, 5] = float("nan")
+        for i in range(n):
+            p = i
+            while p > bad:
+                p = st["parent_slot"][p]
+            hit[i, 8:16] = p == bad and st["mask"][i] != 0
+    else:
+        x[:, :, bad, 3, 7] = float("inf")
+        x[:, :, n + 1] = float("nan")
+        hit[bad, 3] = True
+    r.dec.tree_attn(0, layers, qs, x, out[1], r.scale)
+    a, b = (from_dev(o)[:, 0] for o in out)
+    assert hit.any() and np.isnan(b[:, hit]).all()
+    assert np.array_equal(a[:, ~hit], b[:, ~hit]) and np.isfinite(a).all() and not a[:, n:].any()
+    r.dec.close()

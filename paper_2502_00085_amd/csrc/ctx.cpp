@@ -9,6 +9,7 @@
 #include <utility>
 #include <vector>
 
+#include "node_bound.h"
 #include "td_internal.h"
 
 struct td_ctx {
@@ -22,8 +23,7 @@ struct td_ctx {
                                        //   (for the layers not yet written)
   std::vector<int32_t> leaf_depth;     // per trie: depth of its live leaves (mirrors the
                                        //   device header; tells which appends collect)
-  std::vector<int32_t> nodes;          // per trie: an upper bound of its stored nodes (exact after
-                                       //   init_prompt, load_state and read_state)
+  std::vector<td::NodeBound> start;    // per trie: its size when it was initialised or loaded
   int splits_override = 0;             // TD_ATTN_SPLITS (tuning): WGs per attention unit
   hipEvent_t ev[4][2] = {};             // td_set_kernel_events: per td_phase, the
                                        //   kernel-timestamp events of its next run
@@ -73,10 +73,32 @@ td_status check_ready(td_ctx* c) {
   return TD_OK;
 }
 
-// A bound on the nodes of any trie of the context (what an attention call may have to read).
-long max_nodes(const td_ctx* c) {
-  long n = 0;
-  for (int32_t x : c->nodes) n = n > x ? n : x;
+td::TrieShape shape_of(const td::DevState& s) { return {s.b, s.W, s.G, s.cap}; }
+
+// A call into a graph capture is replayed on whatever the trie has become.
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
+// A bound on the nodes of any trie of the context when a call on this stream runs.
+long max_nodes(const td_ctx* c, bool captured) {
+  long n = 1;
+  for (int t = 0; t < c->dev.T; ++t)
+    n = std::max(n, (captured ? td::node_limit : td::node_bound)(c->start[t], shape_of(c->dev), c->leaf_depth[t]));
+  return n;
+}
+
+// An estimate of the longest key range of a block of `queries` query nodes.  (Of the trie as it is,
+// also under capture: a trie that grows past it runs on the kernel of shorter ranges.)
+long max_keys(const td_ctx* c, int queries) {
+  long n = 1;
+  for (int t = 0; t < c->dev.T; ++t) {
+    const long nodes = td::node_bound(c->start[t], shape_of(c->dev), c->leaf_depth[t]);
+    n = std::max(n, td::window_keys(c->start[t], shape_of(c->dev), c->leaf_depth[t], nodes, queries));
+  }
   return n;
 }
 
@@ -192,7 +214,7 @@ td_status td_create(const td_desc* d, td_ctx** out) {
   }
   c->inited.assign(s.T, 0);
   c->leaf_depth.assign(s.T, 0);
-  c->nodes.assign(s.T, 0);
+  c->start.assign(s.T, td::NodeBound());
   c->layer_written.assign(s.L, 0);
   if (const char* sp = getenv("TD_ATTN_SPLITS")) c->splits_override = atoi(sp) > 0 ? (atoi(sp) < 64 ? atoi(sp) : 64) : 0;
   *out = c;
@@ -227,7 +249,7 @@ td_status td_init_prompt(td_ctx* c, const int32_t* h_plen, const int32_t* d_toke
   c->inited.assign(c->dev.T, 1);
   for (int t = 0; t < c->dev.T; ++t) {
     c->leaf_depth[t] = h_plen[t] - 1;
-    c->nodes[t] = h_plen[t];
+    c->start[t] = {h_plen[t], h_plen[t] - 1, 0, h_plen[t]};
   }
   c->pending = c->moves_pending = false;
   c->layer_written.assign(c->dev.L, 0);
@@ -251,7 +273,8 @@ td_status trie_attn_decode(td_ctx* c, int32_t layer_begin, int32_t n_layers, con
   if (c->pending && (!aligned16(d_k_new) || !aligned16(d_v_new)))
     return fail(c, TD_EINVAL, "k_new / v_new must be 16-byte aligned");
   if (!(scale > 0.0f) || !std::isfinite(scale)) return fail(c, TD_EINVAL, "scale must be finite and > 0");
-  const td::AttnKernel kernel = td::attn_kernel(s, c->desc.attn_impl, n_layers, max_nodes(c));
+  const long nodes = max_nodes(c, capturing(st));
+  const td::AttnKernel kernel = td::attn_kernel(s, c->desc.attn_impl, n_layers, nodes);
   const bool mfma = kernel == td::AttnKernel::kMfma;
   td::AttnArgs a{};
   a.q = d_q;
@@ -269,7 +292,7 @@ td_status trie_attn_decode(td_ctx* c, int32_t layer_begin, int32_t n_layers, con
     a.rb_per_wg = 2;
     a.row_blocks = 1;
   }
-  const td::AttnSplits sp = td::attn_splits(kernel, s, n_layers, a.row_blocks, a.row_blocks32, max_nodes(c));
+  const td::AttnSplits sp = td::attn_splits(kernel, s, n_layers, a.row_blocks, a.row_blocks32, nodes);
   a.splits = c->splits_override > 0 ? c->splits_override : sp.splits;
   a.all_splits = c->splits_override > 0 ? 1 : 0;
   const long units = (long)s.T * n_layers * s.Hkv * a.row_blocks32;  // (partials per 32-row block)
@@ -371,16 +394,14 @@ td_status trie_tree_attn(td_ctx* c, int32_t layer_begin, int32_t n_layers, int32
     a.splits = 1;
     a.xcd_group = a.row_blocks > 1 && ((long)s.T * n_layers * s.Hkv) % 8 == 0 ? 1 : 0;
     c->ev[TD_PHASE_ATTN][0] = c->ev[TD_PHASE_ATTN][1] = nullptr;
-    // (a bound on a block's key range: the trie, or a window before each of its queries)
-    const long keys = s.W > 0 ? std::min(max_nodes(c), (long)s.W + tpb) : max_nodes(c);
-    hipError_t e = td::launch_attn_tree(s, a, keys, st, ev0, ev1);
+    hipError_t e = td::launch_attn_tree(s, a, max_keys(c, tpb / (s.Hq / s.Hkv) + 1), st, ev0, ev1);
     if (e != hipSuccess) return hip_fail(c, e, "trie_tree_attn launch");
     return TD_OK;
   }
   const int rpb = td::attn_mfma_rows_per_block();
   a.row_blocks = (q_max * (s.Hq / s.Hkv) + rpb - 1) / rpb;
   a.row_blocks32 = a.row_blocks;
-  const td::AttnSplits sp = td::attn_mfma_splits(s, n_layers, a.row_blocks, a.row_blocks, max_nodes(c));
+  const td::AttnSplits sp = td::attn_mfma_splits(s, n_layers, a.row_blocks, a.row_blocks, max_nodes(c, capturing(st)));
   a.splits = c->splits_override > 0 ? c->splits_override : sp.splits;
   a.all_splits = c->splits_override > 0 ? 1 : 0;
   const long units = (long)s.T * n_layers * s.Hkv * a.row_blocks;
@@ -430,7 +451,6 @@ static void note_append(td_ctx* c) {
   bool collects = false;
   for (int t = 0; t < c->dev.T; ++t) {
     ++c->leaf_depth[t];
-    c->nodes[t] = std::min(c->nodes[t] + c->dev.b, c->dev.cap);
     collects = collects || (c->leaf_depth[t] + 1) % c->dev.G == 0;
   }
   c->pending = true;
@@ -510,7 +530,6 @@ td_status td_read_state(td_ctx* c, int32_t trie, td_state* o) {
     o->parent_slot[i] = o->parent_slot[i] >= 0 ? o->parent_slot[i] - h.base : -1;
   for (int j = 0; j < h.n_live; ++j) o->leaf_slot[j] = h.n_nodes - h.n_live + j;
   c->leaf_depth[trie] = h.leaf_depth;
-  c->nodes[trie] = h.n_nodes;
   o->n_nodes = h.n_nodes;
   o->n_live = h.n_live;
   o->base = h.base;
@@ -592,7 +611,7 @@ td_status td_load_state(td_ctx* c, int32_t trie, const td_state* in) {
   if (e != hipSuccess) return hip_fail(c, e, "td_load_state");
   c->inited[trie] = 1;
   c->leaf_depth[trie] = h.leaf_depth;
-  c->nodes[trie] = N;
+  c->start[trie] = {N, h.leaf_depth, in->depth[0], n_shared > 0 ? in->depth[n_shared - 1] + 1 : 0};
   if (!others) {  // (with other tries the step's state is theirs, and kv_pending agrees with it)
     c->pending = in->kv_pending != 0;
     c->moves_pending = false;

@@ -71,9 +71,10 @@ typedef enum {
 typedef enum { TD_F32 = 0, TD_BF16 = 1 } td_dtype;
 
 /* Attention kernel choice: AUTO = bf16 at head_dim 64, 96 or 128 -> matrix-core (MFMA)
- * kernel, otherwise (fp32, or another head_dim) the fp32 matrix-instruction kernel
- * (bf16 past head_dim 128 in small calls of few query rows: the vector-ALU kernel).  VALU
- * forces the vector-ALU kernel (the cross-check of both), MFMA the matrix-core kernel
+ * kernel, otherwise (fp32, or another head_dim) the fp32 matrix-instruction kernel or,
+ * past head_dim 128 or 16 query rows per KV head, the vector-ALU kernel, whichever an
+ * estimate from the call's sizes gives less work.  VALU forces the vector-ALU kernel (the
+ * cross-check of both), MFMA the matrix-core kernel
  * (which requires bf16 and head_dim 64, 96 or 128, else td_create returns TD_EUNSUPPORTED). */
 typedef enum { TD_ATTN_AUTO = 0, TD_ATTN_VALU = 1, TD_ATTN_MFMA = 2 } td_attn_impl;
 

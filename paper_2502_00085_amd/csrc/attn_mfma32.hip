@@ -16,7 +16,7 @@
 // What bounds it: HBM, when the rows fill the block (32 rows at d = 128 need 16 bytes per
 // clock and CU of K/V at the full fp32 matrix rate, more than HBM delivers), else latency.
 // The vector-ALU kernel spends about 45 instructions per 4 nodes and query row and reads each
-// node once per 8 rows; it is left as the cross-check (TD_ATTN_VALU).  Measured, 8 layers of
+// node once per 8 rows; attn_kernel below says where it still is the better one.  Measured, 8 layers of
 // 32 q / 8 KV heads at d = 128, 8 beams, 2,080 nodes in fp32 (139 MB), merge included: 293 us
 // there, 48 us here (2.9 TB/s); bf16 at d = 32, 16 beams: 192 us and 27 us.  Error against
 // 64 bits over d = 32 .. 256: 1.3e-7 .. 2.0e-7, there 1.3e-7 .. 2.7e-7.
@@ -40,10 +40,13 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 constexpr float kNegBig32 = -1.0e30f;
 constexpr int kTile32 = 16;  // nodes per wave tile
 
+// Waves of a WG over rt 16-row tiles: past these d, 8 waves' merge buffers exceed the LDS, or their
+// registers the file.
+constexpr int waves32(int d, int rt) { return d > (rt == 2 ? 128 : 192) ? 4 : 8; }
+
 template <typename T, int D, int RT>
 struct Cfg32 {
-  // (past these d, 8 waves' merge buffers exceed the LDS, or their registers the file)
-  static constexpr int NW = D > (RT == 2 ? 128 : 192) ? 4 : 8;
+  static constexpr int NW = waves32(D, RT);
   static constexpr int ROWS = 16 * RT;
   static constexpr int EPC = 16 / (int)sizeof(T);       // elements per 16-byte chunk
   static constexpr int CPR = D / EPC;                   // chunks per node row
@@ -460,10 +463,59 @@ hipError_t launch_rt(const DevState& s, const AttnArgs& a, dim3 grid, hipStream_
 // 32 query rows per WG, or 16 when there are no more.
 int attn_mfma32_rows_per_block(const DevState& s) { return s.b * (s.Hq / s.Hkv) <= 16 ? 16 : 32; }
 
+// Nodes of one round of a WG: a tile per wave.
+static int round_nodes32(const DevState& s) {
+  return waves32(s.D, attn_mfma32_rows_per_block(s) / 16) * kTile32;
+}
+
 // (a trie of at most one tile per wave of a WG needs no split, no partials and no merge launch)
 int attn_mfma32_splits(const DevState& s, int n_layers, int row_blocks, long max_nodes) {
-  const long need = (max_nodes + 8 * kTile32 - 1) / (8 * kTile32);
+  const long round = round_nodes32(s), need = (max_nodes + round - 1) / round;
   return (int)std::max(1l, std::min<long>(attn_choose_splits(s, n_layers, row_blocks), need));
+}
+
+// bf16 at the bf16 kernel's head dims: that one.  Else this kernel or the vector-ALU one, by an
+// estimate of either's chain of dependent work, in units of about 0.3 us.
+//
+//   vector ALU      its iterations (16 nodes of a WG's split) times 1 + 0.75 per query row of its
+//                   block, twice as long for each further 512 WGs
+//   this kernel     16 per round of tiles at d = 256 and 16 query rows (in proportion for other d;
+//                   twice that for 32 rows), once per 256 WGs (its LDS leaves room for one per CU);
+//                   a split launch: 8 more, for the merge of its partials
+//
+// This one wins wherever the rows fill its tiles and the nodes its waves.  It loses where a tile
+// round is long beside the little there is to do: d past 128, where a WG has 4 waves and multiplies
+// 16 or 32 rows whether they exist or not, and 32 rows at d = 96 and 128 in small calls.  One of its
+// WGs with one round of 16 rows answers first at any d, and at d <= 128 no call of up to 16 rows was
+// slower on it.
+//
+// Measured over 16,349 one-layer calls (both types, d = 64 .. 256, 1 .. 96 rows, 1 .. 512 units of 17
+// .. 12,000 nodes), us, vector ALU and this kernel:
+//   d = 256  32 rows, 1 unit, 190 nodes  12.3, 20.3 (bf16)     1 row, 352 units, 330 nodes  34.3, 79.6 (bf16)
+//            16 rows, 24 units, 600 nodes  30.8, 17.2 (bf16)   4 rows, 128 units, 3,000 nodes  168, 152 (bf16)
+//   d = 160  6 rows, 1 unit, 190 nodes  10.9, 13.2; 3,000 nodes  22.9, 17.1 (bf16)
+//   d = 128  32 rows, 1 unit, 190 nodes  13.1, 16.4; 800 nodes  18.6, 15.9 (fp32)
+// Over 6,529 other ones its choice takes 0.7 % longer than the faster kernel in the mean; always this
+// one 5 %, always the vector ALU 55 %.
+AttnKernel attn_kernel(const DevState& s, int attn_impl, int n_layers, long max_nodes) {
+  if (attn_impl == TD_ATTN_VALU) return AttnKernel::kValu;
+  if (s.dtype == TD_BF16 && mfma_head_dim(s.D)) return AttnKernel::kMfma;
+  const int rows = s.b * (s.Hq / s.Hkv), tiles = attn_mfma32_rows_per_block(s) / 16;
+  if (s.D <= 128 && tiles == 1) return AttnKernel::kMfma32;
+  const long units = (long)s.T * n_layers * s.Hkv;
+  auto up = [](long x, long y) { return (x + y - 1) / y; };
+
+  const int vrows = attn_valu_rows_per_block(s.D), vblocks = (int)up(rows, vrows);
+  const int vsplits = attn_choose_splits(s, n_layers, vblocks);
+  const double valu = up(max_nodes, 16 * vsplits) * std::max(1.0, units * vblocks * vsplits / 512.0) *
+                      (1.0 + 0.75 * std::min(rows, vrows));
+
+  const int blocks = (int)up(rows, 16 * tiles);
+  const int splits = attn_mfma32_splits(s, n_layers, blocks, max_nodes);
+  const long rounds = up(max_nodes, (long)splits * round_nodes32(s)), wgs = units * blocks * splits;
+  if (splits == 1 && rounds == 1 && tiles == 1 && wgs <= 256) return AttnKernel::kMfma32;
+  const double mfma = 16.0 * rounds * up(wgs, 256) * tiles * s.D / 256 - (splits == 1 ? 8.0 : 0.0);
+  return valu <= mfma ? AttnKernel::kValu : AttnKernel::kMfma32;
 }
 
 hipError_t launch_attn_mfma32(const DevState& s, const AttnArgs& a, hipStream_t st, hipEvent_t ev0,

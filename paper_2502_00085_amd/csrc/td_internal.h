@@ -148,23 +148,10 @@ struct AttnSplits {
 AttnSplits attn_mfma_splits(const DevState& s, int n_layers, int row_blocks, int row_blocks32, long max_nodes);
 int attn_mfma32_rows_per_block(const DevState& s);
 int attn_mfma32_splits(const DevState& s, int n_layers, int row_blocks, long max_nodes);
-// The decode attention kernel of a call: the bf16 matrix-core one where it is implemented; the
-// fp32 matrix-instruction one for fp32 and the other head dims; the vector-ALU one where the
-// caller forces it, and for bf16 past d = 128 in small calls of up to 16 query rows per KV head,
-// which are bound by the latency of one WG's tiles and merge.  Measured, 6 rows, one unit, vector
-// ALU against fp32 matrix instructions: d = 160: 40 nodes 10.3 and 9.0 us, 190 nodes 10.9 and 13.4,
-// 800 nodes 13.7 and 13.3; d = 256: 190 nodes 12.2 and 19.5, 800 nodes 15.2 and 18.7, 3,000 nodes
-// 25.6 and 25.2; 48 units: d = 160, 190 nodes 16.6 and 13.9; d = 256, 800 nodes 38.9 and 47.8.
+// The decode attention kernel of a call (attn_mfma32.hip says where the line lies).  max_nodes: a
+// bound on the nodes of any trie.
 enum class AttnKernel { kMfma, kMfma32, kValu };
-inline AttnKernel attn_kernel(const DevState& s, int attn_impl, int n_layers, long max_nodes) {
-  if (attn_impl == TD_ATTN_VALU) return AttnKernel::kValu;
-  if (s.dtype == TD_BF16 && mfma_head_dim(s.D)) return AttnKernel::kMfma;
-  const bool wide = s.D > 192;  // (half the waves per WG)
-  if (s.dtype == TD_BF16 && s.D > 128 && s.b * (s.Hq / s.Hkv) <= 16 && max_nodes > (wide ? 64 : 128) &&
-      max_nodes <= (wide ? 2048 : 512) && (long)s.T * n_layers * s.Hkv <= (wide ? 48 : 8))
-    return AttnKernel::kValu;
-  return AttnKernel::kMfma32;
-}
+AttnKernel attn_kernel(const DevState& s, int attn_impl, int n_layers, long max_nodes);
 inline int attn_rows_per_block(const DevState& s, AttnKernel k) {
   return k == AttnKernel::kMfma     ? attn_mfma_rows_per_block()
          : k == AttnKernel::kMfma32 ? attn_mfma32_rows_per_block(s)

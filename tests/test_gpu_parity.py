@@ -62,7 +62,7 @@ def test_one_layer_calls_fused_selection():
 
 
 def test_one_layer_calls_fp32_vector_kernel():
-    # fp32 K/V: the vector-ALU attention kernel, with node splits and the fp32 merge
+    # fp32 K/V in small calls, with the fp32 merge (64 query rows and a few nodes: the vector-ALU kernel)
     layer_case(small(n_layers=3, head_dim=64, dtype="f32", steps=6), seed=45, calls=[0, 1, 3])
 
 
@@ -313,12 +313,13 @@ def test_one_row_block_half_wgs_window_deferred_collection_fused():
                    qkv_std=1.0 / np.sqrt(96.0), steps=12), seed=85, fused=True)
 
 
-# head dims outside the matrix-core kernels' 64, 96 and 128 run on the vector-ALU kernel
-# (bf16 storage, fp32 arithmetic; 4-row blocks past d = 128)
+# head dims outside the matrix-core kernels' 64, 96 and 128: the vector-ALU kernel (bf16 storage,
+# fp32 arithmetic; 4-row blocks past d = 128), and the kernel that is chosen there
+@pytest.mark.parametrize("impl", [B.TD_ATTN_VALU, B.TD_ATTN_AUTO])
 @pytest.mark.parametrize("d", [32, 160, 192, 224, 256])
-def test_head_dims_on_the_vector_alu_kernel(d):
+def test_head_dims_on_the_vector_alu_kernel(d, impl):
     run_case(small(n_layers=2, n_q_heads=8, n_kv_heads=2, head_dim=d, beam_width=4, prompt_min=40,
-                   prompt_max=40, vocab=400, qkv_std=1.0 / np.sqrt(d), steps=6), seed=90 + d)
+                   prompt_max=40, vocab=400, qkv_std=1.0 / np.sqrt(d), steps=6), seed=90 + d, impl=impl)
 
 
 def test_head_dim_256_fp32_window_splits_layer_calls():

@@ -12,8 +12,9 @@
 //
 // Runs where the caller forces it (TD_ATTN_VALU, the cross-check of the bf16 matrix-core kernel
 // and of the fp32 matrix-instruction kernel), and where attn_kernel (attn_mfma32.hip) estimates it
-// faster than the latter: wide heads with few query rows or little to do.  Any head dim that is a multiple of 32 up to 256; blocks of 4 rows past d = 128, so that the
-// rows' query and output registers stay within the register file.
+// faster than the latter: wide heads with few query rows or little to do.  Any head dim that is a
+// multiple of 32 up to 256; blocks of 4 rows past d = 128, so that the rows' query and output
+// registers stay within the register file.
 #include "attn_common.h"
 
 namespace td {

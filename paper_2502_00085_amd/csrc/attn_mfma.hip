@@ -27,6 +27,7 @@
 // launch merges (attn_combine.hip).  Template variants: TREE (rows are arbitrary query
 // nodes) and RB = 2 (one WG over two 32-row blocks).
 #include <algorithm>
+#include <numeric>
 #include <type_traits>
 
 #include "attn_common.h"
@@ -732,23 +733,39 @@ int attn_choose_splits(const DevState& s, int n_layers, int row_blocks) {
 }
 
 // The bf16 kernel's splits and WGs.  max_nodes, the host's bound on a trie's nodes, says how many
-// WGs a span can use (a trie that fits one WG needs no partials and no merge launch).  8-wave
-// WGs, one per CU, never more than the CUs (264 of them ran two rounds; 24 draft nodes in 11
+// WGs a span can use.  A trie of a tile per wave is not split: it needs no partials and no merge
+// launch (8 units at d = 128, 20 .. 250 nodes: 8.6 .. 10.3 us, split 11.3 .. 11.6; at 500 nodes 11.7
+// and 11.6).  (With two row blocks per WG the ends of a WG are longer: 6 tiles; 180 nodes 13.7 us
+// and 14.0, 250 nodes 16.2 and 14.1.)
+//
+// 8-wave WGs, one per CU, never more than the CUs (264 of them ran two rounds; 24 draft nodes in 11
 // splits of 24 units: 17.9 us, in 10: 17.7).  Where they would leave half of the CUs idle, 4-wave
 // WGs instead (8 units of 2,140 nodes: 9 WGs each, 14.1 us; 17 half-size WGs, 12.9), but not
 // where all CUs are busy: there the smaller WGs only make more partials (32 units of 2,700 nodes,
 // 8 splits: 16.7 us; 16 half-size ones: 19.2).  Past 128 units two 8-wave WGs each do not fit
 // one round: 4-wave ones.
-AttnSplits attn_mfma_splits(const DevState& s, int n_layers, int row_blocks, int row_blocks32, long max_nodes) {
-  const long units = (long)s.T * n_layers * s.Hkv * row_blocks;
-  if (units >= 192) return {1, false};
-  const long tiles = (max_nodes + 31) / 32, fit = s.attn_pairs_max / (units / row_blocks * row_blocks32);
+//
+// Several row blocks of one WG each (decode) stream the same nodes, from one XCD's L2 where the ranges
+// divide over the 8 XCDs (AttnArgs::xcd_group): splits of more than a tile per wave are rounded down
+// to a number that lets them (28 ranges of 7,000 nodes under 3 row blocks: 3 splits 57 us, 2 splits
+// 37; 12 ranges under 4: 5 splits 37 us, 4 splits 26), or 4-wave WGs taken where only theirs do (22
+// ranges of 10,000 nodes: 3 splits 69 us, 4 half-size ones 47).  Small query sets, bound by their
+// visibility test, lose more by fewer WGs.
+AttnSplits attn_mfma_splits(const DevState& s, int n_layers, int row_blocks, int row_blocks32, long max_nodes, bool tree) {
+  const long ranges = (long)s.T * n_layers * s.Hkv, units = ranges * row_blocks;
+  const long tiles = (max_nodes + 31) / 32;
+  if (units >= 192 || tiles <= (row_blocks32 > row_blocks ? 6 : kNW)) return {1, false};
+  const long fit = s.attn_pairs_max / (ranges * row_blocks32);
+  const long step = row_blocks > 1 && !tree ? 8 / std::gcd(ranges, 8l) : 1;
+  auto needs = [&](int nw) { return std::max((tiles + nw - 1) / nw, std::min(8l, (tiles + nw / 2 - 1) / (nw / 2))); };
   auto best = [&](long wgs, long most, int nw) {
-    const long need = std::max((tiles + nw - 1) / nw, std::min(8l, (tiles + nw / 2 - 1) / (nw / 2)));
-    return std::max(1l, std::min({wgs / units, need, fit, most}));
+    const long need = needs(nw), n = std::max(1l, std::min({wgs / units, need, fit, most}));
+    return n < need && n > step ? n / step * step : n;
   };
   const long full = best(kCUs, 16, kNW), half = best(2 * kCUs, 32, kNW / 2);
-  return units * full < kCUs / 2 || units > kCUs / 2 ? AttnSplits{(int)half, half > 1} : AttnSplits{(int)full, false};
+  const bool apart = full < needs(kNW) && full % step != 0 && half % step == 0;
+  return units * full < kCUs / 2 || units > kCUs / 2 || apart ? AttnSplits{(int)half, half > 1}
+                                                              : AttnSplits{(int)full, false};
 }
 
 hipError_t launch_attn_mfma(const DevState& s, const AttnArgs& a, hipStream_t st, hipEvent_t ev0,

@@ -401,7 +401,7 @@ td_status trie_tree_attn(td_ctx* c, int32_t layer_begin, int32_t n_layers, int32
   const int rpb = td::attn_mfma_rows_per_block();
   a.row_blocks = (q_max * (s.Hq / s.Hkv) + rpb - 1) / rpb;
   a.row_blocks32 = a.row_blocks;
-  const td::AttnSplits sp = td::attn_mfma_splits(s, n_layers, a.row_blocks, a.row_blocks, max_nodes(c, capturing(st)));
+  const td::AttnSplits sp = td::attn_mfma_splits(s, n_layers, a.row_blocks, a.row_blocks, max_nodes(c, capturing(st)), true);
   a.splits = c->splits_override > 0 ? c->splits_override : sp.splits;
   a.all_splits = c->splits_override > 0 ? 1 : 0;
   const long units = (long)s.T * n_layers * s.Hkv * a.row_blocks;

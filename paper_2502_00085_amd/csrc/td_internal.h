@@ -145,7 +145,7 @@ struct AttnSplits {
   int splits;
   bool half_wgs;  // (AttnArgs::half_wgs)
 };
-AttnSplits attn_mfma_splits(const DevState& s, int n_layers, int row_blocks, int row_blocks32, long max_nodes);
+AttnSplits attn_mfma_splits(const DevState& s, int n_layers, int row_blocks, int row_blocks32, long max_nodes, bool tree);
 int attn_mfma32_rows_per_block(const DevState& s);
 int attn_mfma32_splits(const DevState& s, int n_layers, int row_blocks, long max_nodes);
 // The decode attention kernel of a call (attn_mfma32.hip says where the line lies).  max_nodes: a
@@ -161,7 +161,7 @@ inline int attn_rows_per_block(const DevState& s, AttnKernel k) {
 // them); max_nodes: a bound on the nodes of any trie.
 inline AttnSplits attn_splits(AttnKernel k, const DevState& s, int n_layers, int row_blocks, int row_blocks32,
                               long max_nodes) {
-  if (k == AttnKernel::kMfma) return attn_mfma_splits(s, n_layers, row_blocks, row_blocks32, max_nodes);
+  if (k == AttnKernel::kMfma) return attn_mfma_splits(s, n_layers, row_blocks, row_blocks32, max_nodes, false);
   if (k == AttnKernel::kMfma32) return {attn_mfma32_splits(s, n_layers, row_blocks, max_nodes), false};
   return {attn_choose_splits(s, n_layers, row_blocks), false};
 }

@@ -13,11 +13,14 @@ from test_gpu_parity import small
 pytestmark = pytest.mark.gpu
 
 
-# (tries, beams, q heads, KV heads, prompt, window): units of 1 .. 160, rows of 1 .. 96 per KV head
+# (tries, beams, q heads, KV heads, prompt, window): units of 1 .. 160, rows of 1 .. 96 per KV head;
+# tries that grow past the unsplit ones (256 nodes, 192 under two row blocks per workgroup); three and
+# four row blocks over 5, 6 and 12 ranges, which do not divide over the XCDs by themselves
 @pytest.mark.parametrize("T,b,hq,hkv,P,W", [
     (1, 1, 1, 1, 5, 0), (1, 4, 4, 1, 31, 0), (1, 4, 8, 2, 127, 0), (1, 8, 32, 8, 1025, 0), (1, 8, 8, 2, 4200, 0),
     (1, 16, 8, 2, 700, 0), (2, 24, 8, 2, 129, 0), (2, 24, 8, 2, 90, 33), (1, 3, 8, 8, 2300, 1100),
-    (16, 4, 8, 8, 70, 0), (20, 4, 16, 8, 150, 0)])
+    (16, 4, 8, 8, 70, 0), (20, 4, 16, 8, 150, 0), (1, 8, 8, 2, 245, 0), (1, 16, 8, 2, 180, 0), (1, 24, 24, 6, 700, 0),
+    (5, 25, 4, 1, 400, 0), (3, 24, 16, 4, 330, 200)])
 @pytest.mark.parametrize("d", [64, 128])
 def test_decode(T, b, hq, hkv, P, W, d):
     w = small(n_tries=T, beam_width=b, n_q_heads=hq, n_kv_heads=hkv, prompt_min=max(1, P - 3 * (T - 1)), prompt_max=P,
@@ -31,7 +34,8 @@ def test_decode(T, b, hq, hkv, P, W, d):
     r.dec.close()
 
 
-@pytest.mark.parametrize("hq,hkv,P,W,n", [(2, 2, 20, 0, 3), (8, 2, 300, 0, 9), (32, 8, 1100, 0, 24), (8, 2, 600, 100, 31)])
+@pytest.mark.parametrize("hq,hkv,P,W,n", [(2, 2, 20, 0, 3), (8, 2, 300, 0, 9), (32, 8, 1100, 0, 24), (8, 2, 600, 100, 31),
+                                          (8, 2, 225, 0, 20), (24, 6, 700, 0, 30)])
 def test_small_query_sets(hq, hkv, P, W, n):
     tree.run_tree(tree.small(prompt_min=P, prompt_max=P, n_q_heads=hq, n_kv_heads=hkv, window=W, steps=4, beam_width=6),
                   seed=32, pick=lambda tr, g: tree.every_node(tr, g)[-n:], layer_calls=[0, 1, 2])

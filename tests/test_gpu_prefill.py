@@ -1,6 +1,6 @@
 """The prefill-shaped tree attention where its launch shapes and its softmax shift can go wrong:
-launches of more than 512 row blocks (one group of waves per workgroup), with one unit per XCD
-(the folded block order), row blocks that end inside a tile, and scores whose range makes the
+launches of more than 512 row blocks (one group of waves per workgroup), with one unit per XCD,
+row blocks that end inside a tile, and scores whose range makes the
 shift move again and again.  Against the CPU oracle, at its bf16 tolerance.  And NaN scores."""
 import numpy as np
 import pytest

@@ -44,7 +44,7 @@ namespace {
 constexpr int kTreeWaves = 4;  // (two WGs per CU: their barriers do not wait on each other)
 constexpr int kTreeThreads = kTreeWaves * 64;
 constexpr int kTreeRows = kTreeWaves * 32;  // query rows per WG
-constexpr int kTreeSplitWgs = 512, kTreeSplitWgs64 = 320;       // (see launch_attn_tree)
+constexpr int kTreeRound = 256, kTreeRampWgs = 512, kTreeRampWgs64 = 320;  // (see launch_attn_tree)
 constexpr long kTreeShortKeys = 560, kTreeShortKeys64 = 768;
 constexpr float kTreeNegBig = -1.0e30f;
 constexpr float kTreeSlack = 8.0f;     // a row's shift moves for scores 2^8 above it
@@ -405,17 +405,25 @@ int attn_tree_rows_per_block() { return kTreeRows; }
 // where five of its WGs fit a CU, it holds out longer in launches of several WGs per CU: 600 nodes,
 // 960 blocks, 37.5 and 35.8; 700 nodes, 1,088 blocks, 43.7 and 41.1; 850 nodes, 1,280, 51.7 and 54.0.
 //
-// Two groups per WG where one group per WG leaves CUs with less than two (measured, a call of
-// 32 WGs: 53 us with one group, 44 with two; of 320 WGs at d = 96: 32 and 28; of 512 at d = 128:
-// 44.6 and 42.8; beyond one round of single groups the two-group WG, whose barrier ties 8 waves,
-// loses: 64 against 71 us for 528 WGs).  At d = 64 a round is more single groups: 320 WGs, 24.6
-// and 23.7 us, but 384, 27.2 and 28.0.
-hipError_t launch_attn_tree(const DevState& s, const AttnArgs& a, long max_keys, hipStream_t st, hipEvent_t ev0,
-                            hipEvent_t ev1) {
+// Two groups per WG, whose barrier ties 8 waves and of which a CU holds one, where all of them run at
+// once: up to 256 (100 queries of 1,700 nodes, 256 blocks, 44 us against 50 with one group; 400
+// queries, 416 blocks, 75 against 64).  Where the blocks' ranges rise from nothing to all (every node
+// a query, no window, the blocks of a unit on one XCD, the longest first), the short ones fill the
+// second round: up to 512 (1,700 nodes, 440 blocks, 46 and 51 us; 850 nodes, 464 blocks, 35.2 and
+// 36.9; past that, 528 blocks, 50.0 and 45.3), at d = 64, where more single groups fit a CU, up to
+// 320 (24.6 us with one group, 23.7 with two; 384 blocks, 27.2 and 28.0).  Without XCDs of their own
+// the units follow one another, each from its longest block: the second round may hold no more than
+// the last unit's (6 units of 49 blocks, 89 and 75 us; 12 units of 24, 35.3 and 37.6).
+hipError_t launch_attn_tree(const DevState& s, const AttnArgs& a, long max_keys, bool ramp, hipStream_t st,
+                            hipEvent_t ev0, hipEvent_t ev1) {
   const int wgs = s.T * a.n_layers * s.Hkv * a.row_blocks;
-  if (max_keys <= kTreeShortKeys || (s.D == 64 && max_keys <= kTreeShortKeys64 && wgs > kTreeSplitWgs64))
+  const int most = !ramp         ? kTreeRound
+                   : !a.xcd_group ? kTreeRound + a.row_blocks
+                   : s.D == 64    ? kTreeRampWgs64
+                                  : kTreeRampWgs;
+  const bool split = wgs <= most;
+  if (max_keys <= kTreeShortKeys || (s.D == 64 && max_keys <= kTreeShortKeys64 && !split))
     return launch_attn_tree_short(s, a, st, ev0, ev1);
-  const bool split = wgs <= (s.D == 64 ? kTreeSplitWgs64 : kTreeSplitWgs);
   const dim3 grid(wgs), block(split ? 2 * kTreeThreads : kTreeThreads);
 #define LAUNCH_TREE(DD)                                                                               \
   (split ? hipExtLaunchKernelGGL((k_attn_tree<DD, 2>), grid, block, 0, st, ev0, ev1, 0, s, a)          \

@@ -394,7 +394,10 @@ td_status trie_tree_attn(td_ctx* c, int32_t layer_begin, int32_t n_layers, int32
     a.splits = 1;
     a.xcd_group = a.row_blocks > 1 && ((long)s.T * n_layers * s.Hkv) % 8 == 0 ? 1 : 0;
     c->ev[TD_PHASE_ATTN][0] = c->ev[TD_PHASE_ATTN][1] = nullptr;
-    hipError_t e = td::launch_attn_tree(s, a, max_keys(c, tpb / (s.Hq / s.Hkv) + 1), st, ev0, ev1);
+    // (nearly every node a query, and no window that cuts their ranges)
+    const long nodes = max_nodes(c, false);
+    const bool ramp = q_max >= nodes - nodes / 8 && (s.W <= 0 || s.W >= nodes);
+    hipError_t e = td::launch_attn_tree(s, a, max_keys(c, tpb / (s.Hq / s.Hkv) + 1), ramp, st, ev0, ev1);
     if (e != hipSuccess) return hip_fail(c, e, "trie_tree_attn launch");
     return TD_OK;
   }

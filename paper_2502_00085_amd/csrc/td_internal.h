@@ -132,9 +132,10 @@ hipError_t launch_attn_combine(const DevState& s, const AttnArgs& a, int rows_pe
                                hipEvent_t ev0, hipEvent_t ev1);
 int attn_mfma_rows_per_block();
 int attn_tree_rows_per_block();
-// (max_keys: an estimate of a row block's key range; it chooses the kernel, each takes any range)
-hipError_t launch_attn_tree(const DevState& s, const AttnArgs& a, long max_keys, hipStream_t st, hipEvent_t ev0,
-                            hipEvent_t ev1);
+// (max_keys: an estimate of a row block's key range; ramp: the blocks' ranges run from short to the
+// whole trie.  They choose the kernel and its WGs; each takes any ranges)
+hipError_t launch_attn_tree(const DevState& s, const AttnArgs& a, long max_keys, bool ramp, hipStream_t st,
+                            hipEvent_t ev0, hipEvent_t ev1);
 hipError_t launch_attn_tree_short(const DevState& s, const AttnArgs& a, hipStream_t st, hipEvent_t ev0,
                                   hipEvent_t ev1);
 int attn_valu_rows_per_block(int d);  // query rows per block at head dim d

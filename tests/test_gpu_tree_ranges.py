@@ -22,6 +22,15 @@ def test_long_ranges(d, hkv, layers, prompt, window):
                    beam_width=6, steps=7, window=window, gc_interval=4), seed=24, pick=every_node)
 
 
+# 257 to 512 row blocks: one group where the blocks are not those of every node, or have no XCD of
+# their own (12 units), two where they are and have
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("tries,hkv,layers,g,prompt,n", [(1, 8, 4, 4, 600, 300), (3, 4, 1, 8, 570, None), (1, 8, 2, 4, 600, None)])
+def test_groups(d, tries, hkv, layers, g, prompt, n):
+    run_tree(small(n_tries=tries, n_layers=layers, prompt_min=prompt, prompt_max=prompt, n_q_heads=g * hkv, n_kv_heads=hkv,
+                   head_dim=d, beam_width=6, steps=3), seed=27, pick=lambda tr, r: every_node(tr, r)[-(n or 10 ** 6):])
+
+
 @pytest.mark.parametrize("d,hkv", [(64, 2), (96, 4), (128, 2)])
 def test_large_scores(d, hkv, monkeypatch):
     # twelve times the usual scale: scores of a row over tens of powers of two

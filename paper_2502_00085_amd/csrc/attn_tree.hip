@@ -34,6 +34,8 @@
 // half beside the softmax of another) measured slower as hipcc schedules it.  Prefill of 2,096
 // nodes at d = 128, 32 q / 8 KV heads, per layer: 85 us -> 62 us in one-layer calls, 50 -> 44 us
 // in a call of 16 layers (782 TFLOP/s); 100 queries in one-layer calls: 68 -> 44 us.
+#include <algorithm>
+
 #include "attn_common.h"
 #include "mfma_tile.h"
 
@@ -408,19 +410,17 @@ int attn_tree_rows_per_block() { return kTreeRows; }
 // Two groups per WG, whose barrier ties 8 waves and of which a CU holds one, where all of them run at
 // once: up to 256 (100 queries of 1,700 nodes, 256 blocks, 44 us against 50 with one group; 400
 // queries, 416 blocks, 75 against 64).  Where the blocks' ranges rise from nothing to all (every node
-// a query, no window, the blocks of a unit on one XCD, the longest first), the short ones fill the
-// second round: up to 512 (1,700 nodes, 440 blocks, 46 and 51 us; 850 nodes, 464 blocks, 35.2 and
-// 36.9; past that, 528 blocks, 50.0 and 45.3), at d = 64, where more single groups fit a CU, up to
-// 320 (24.6 us with one group, 23.7 with two; 384 blocks, 27.2 and 28.0).  Without XCDs of their own
-// the units follow one another, each from its longest block: the second round may hold no more than
-// the last unit's (6 units of 49 blocks, 89 and 75 us; 12 units of 24, 35.3 and 37.6).
+// a query, no window), a unit's blocks go out longest first and the next unit's after them: the second
+// round may then hold the last unit's blocks and the shortest of the one before (per XCD, where the
+// units have one: 8 units of 55, 46 and 51 us; 16 of 29, 35.2 and 36.9; 64 of 5, 38.3 and 33; without:
+// 6 units of 49, 75 and 89; 3 of 133, 98 and 119; 12 of 24, 37.6 and 35.3), up to 512 blocks in all
+// (528: 50.0 and 45.3), and up to 320 at d = 64, where more single groups fit a CU (23.7 and 24.6;
+// 384 blocks, 28.0 and 27.2).
 hipError_t launch_attn_tree(const DevState& s, const AttnArgs& a, long max_keys, bool ramp, hipStream_t st,
                             hipEvent_t ev0, hipEvent_t ev1) {
   const int wgs = s.T * a.n_layers * s.Hkv * a.row_blocks;
-  const int most = !ramp         ? kTreeRound
-                   : !a.xcd_group ? kTreeRound + a.row_blocks
-                   : s.D == 64    ? kTreeRampWgs64
-                                  : kTreeRampWgs;
+  const int second = (a.row_blocks + a.row_blocks / 4) * (a.xcd_group ? 8 : 1);
+  const int most = ramp ? std::min(kTreeRound + second, s.D == 64 ? kTreeRampWgs64 : kTreeRampWgs) : kTreeRound;
   const bool split = wgs <= most;
   if (max_keys <= kTreeShortKeys || (s.D == 64 && max_keys <= kTreeShortKeys64 && !split))
     return launch_attn_tree_short(s, a, st, ev0, ev1);

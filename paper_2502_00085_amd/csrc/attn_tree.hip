@@ -36,29 +36,21 @@
 // in a call of 16 layers (782 TFLOP/s); 100 queries in one-layer calls: 68 -> 44 us.
 #include <algorithm>
 
-#include "attn_common.h"
-#include "mfma_tile.h"
+#include "attn_tree_common.h"
 
 namespace td {
 
 namespace {
 
-constexpr int kTreeWaves = 4;  // (two WGs per CU: their barriers do not wait on each other)
-constexpr int kTreeThreads = kTreeWaves * 64;
-constexpr int kTreeRows = kTreeWaves * 32;  // query rows per WG
 constexpr int kTreeRound = 256, kTreeRampWgs = 512, kTreeRampWgs64 = 320;  // (see launch_attn_tree)
 constexpr long kTreeShortKeys = 560, kTreeShortKeys64 = 768;
-constexpr float kTreeNegBig = -1.0e30f;
-constexpr float kTreeSlack = 8.0f;     // a row's shift moves for scores 2^8 above it
-constexpr float kTreeMost = 8192.0f;   // ... once 16 of its probabilities add up to more than this
+constexpr float kTreeMost = 8192.0f;  // a row's shift moves once 16 of its probabilities add up to more
 
 template <int D>
-struct TreeCfg {
-  static constexpr int KSTEPS = D / 16;                 // 32x32x16 steps of S^T
-  static constexpr int DT = D / 32;                     // 32-wide d tiles of O^T
-  static constexpr int CPR = D / 8;                     // 16-byte chunks per node row
-  static constexpr int NBLK = CPR / 4;                  // 64-byte blocks per row
-  static constexpr int HALF = 32 * D * 2;               // bytes of 32 K (or V) rows
+struct TreeCfg : TreeGeom<D> {
+  using TreeGeom<D>::CPR;
+  using TreeGeom<D>::NBLK;
+  using TreeGeom<D>::HALF;
   static constexpr int LOADS = 2 * HALF / 16 / kTreeThreads;  // 16-byte loads per thread: K (or V) of a tile
   static_assert(2 * HALF % (16 * kTreeThreads) == 0, "a tile is a whole number of WG loads");
   // load j of a thread is load 0 moved by whole rows (the same rotation), so one offset does
@@ -79,72 +71,25 @@ __global__ __launch_bounds__(KS * kTreeThreads, TreeCfg<D>::WAVES) void k_attn_t
   __shared__ __attribute__((aligned(16))) unsigned char kbuf0[KS * 2 * C::HALF], vbuf0[KS * 2 * C::HALF];
   __shared__ __attribute__((aligned(16))) unsigned char kbuf1[KS * 2 * C::HALF], vbuf1[KS * 2 * C::HALF];
   __shared__ int wred[2][kTreeWaves];  // per wave: deepest query slot + 1, shallowest depth
-  // (trie, layer, KV head) unit and row block; the row blocks of a unit go to one XCD, the deepest
-  // (longest) first.  (Going up again after half of them, so that a CU gets a long and a short block,
-  // measured slower past 66 blocks per XCD: at d = 128, 91 blocks 65.1 us against 53.7, 127 blocks
-  // 175 and 165.)
-  int x = blockIdx.x, unit, rb;
-  if (a.xcd_group) {
-    const int xcd = x % 8, k = x / 8;
-    unit = (k / a.row_blocks) * 8 + xcd;
-    rb = a.row_blocks - 1 - k % a.row_blocks;
-  } else {
-    unit = x / a.row_blocks;
-    rb = a.row_blocks - 1 - x % a.row_blocks;
-  }
-  const int g = unit % s.Hkv, li = (unit / s.Hkv) % a.n_layers, t = unit / (s.Hkv * a.n_layers);
-  const TrieHdr h = s.hdr[t];
+  const TreeUnit u = tree_unit(s, a);
+  const TrieHdr h = s.hdr[u.t];
   const int N = h.n_nodes, base = h.base;
   const int G = s.Hq / s.Hkv;
-  const int lab = a.layer_begin + li;
+  const int lab = a.layer_begin + u.li;
   const int lane = threadIdx.x & 63, tid = threadIdx.x % kTreeThreads;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);               // of its group
   const int group = __builtin_amdgcn_readfirstlane(threadIdx.x / kTreeThreads);
   const int col = lane & 31, hh = lane >> 5;
-  const uint64_t* maskp = s.mask + (size_t)t * s.cap + base;
-  const int32_t* depthp = s.depth + (size_t)t * s.cap + base;
+  const uint64_t* maskp = s.mask + (size_t)u.t * s.cap + base;
+  const int32_t* depthp = s.depth + (size_t)u.t * s.cap + base;
 
-  // this lane's query row
-  const int r = rb * kTreeRows + wave * 32 + col;
-  const int owner = r / G;
-  int slot = r < a.qmax * G ? a.qslots[(size_t)t * a.qmax + owner] : -1;
-  bool row_ok = slot >= 0 && slot < N;
-  uint64_t qmask = 0;
-  int qdepth = -1;
-  if (row_ok) {
-    qmask = maskp[slot];
-    row_ok = qmask != 0ull;
-  }
-  if (row_ok) qdepth = depthp[slot];
-  // the wave's deepest query slot, shallowest and deepest query depth (live rows)
-  int whi = row_ok ? slot + 1 : 0, wdmin = row_ok ? qdepth : INT_MAX, wdmax = row_ok ? qdepth : -1;
-  for (int o = 16; o > 0; o >>= 1) {
-    whi = max(whi, __shfl_xor(whi, o));
-    wdmin = min(wdmin, __shfl_xor(wdmin, o));
-    wdmax = max(wdmax, __shfl_xor(wdmax, o));
-  }
-  whi = __builtin_amdgcn_readfirstlane(whi);
-  wdmin = __builtin_amdgcn_readfirstlane(wdmin);
-  wdmax = __builtin_amdgcn_readfirstlane(wdmax);
-  if (lane == 0) {
-    wred[0][wave] = whi;
-    wred[1][wave] = wdmin;
-  }
-  __syncthreads();
-  int hi = 0, dmin = INT_MAX;
-  for (int w = 0; w < kTreeWaves; ++w) {
-    hi = max(hi, wred[0][w]);
-    dmin = min(dmin, wred[1][w]);
-  }
-  hi = __builtin_amdgcn_readfirstlane(hi);
-  dmin = __builtin_amdgcn_readfirstlane(dmin);
-  // the block's key range: from the window start of its shallowest query to its deepest
-  // query slot (ancestors precede their descendants in slot order)
-  const int lo = __builtin_amdgcn_readfirstlane(hi > 0 ? window_lo(s, t, base, N, dmin) : 0);
+  const TreeRow q = tree_row(s, a, u, N, G, maskp, depthp, wave, col);
+  const int2 range = tree_range(s, u, q, base, N, lane, wave, wred);
+  const int lo = range.x, hi = range.y;
   const int ntiles = hi > lo ? (hi - lo + 63) / 64 : 0;
 
-  const __bf16* kpool = static_cast<const __bf16*>(s.k_pool) + pool_row(s, t, lab, g, base);
-  const __bf16* vpool = static_cast<const __bf16*>(s.v_pool) + pool_row(s, t, lab, g, base);
+  const __bf16* kpool = static_cast<const __bf16*>(s.k_pool) + pool_row(s, u.t, lab, u.g, base);
+  const __bf16* vpool = static_cast<const __bf16*>(s.v_pool) + pool_row(s, u.t, lab, u.g, base);
 
   // Load j of this thread writes 16-byte LDS chunk c = j kTreeThreads + tid of its group's
   // tile's K (and V): tile row c / CPR at physical chunk c % CPR; the K rows of a 32-key half
@@ -189,18 +134,8 @@ __global__ __launch_bounds__(KS * kTreeThreads, TreeCfg<D>::WAVES) void k_attn_t
     if (tb + 64 > h.n_shared) kmk = maskp[nn];  // (before: every mask is all ones)
   };
 
-  // this lane's query row (B operand of S^T): half hh of the row's d range
   bf16x8 qv[C::KSTEPS];
-  {
-    const uint4* qp = reinterpret_cast<const uint4*>(
-        static_cast<const __bf16*>(a.q) +
-        ((((size_t)li * s.T + t) * a.qmax + (row_ok ? owner : 0)) * s.Hq + g * G + r % G) * D + hh * (D / 2));
-#pragma unroll
-    for (int k = 0; k < C::KSTEPS; ++k) {
-      const uint4 v = row_ok ? qp[k] : make_uint4(0, 0, 0, 0);
-      qv[k] = __builtin_bit_cast(bf16x8, v);
-    }
-  }
+  tree_query<D>(s, a, u, q, G, hh, qv);
   // operand read offsets (as in the decode kernel): K rows in MFMA layout, V transposed by
   // 16-lane groups
   const int grp = lane >> 4, tm = (lane & 15) >> 2, tq = lane & 3;
@@ -217,7 +152,6 @@ __global__ __launch_bounds__(KS * kTreeThreads, TreeCfg<D>::WAVES) void k_attn_t
     }
 
   const float scale = a.scale_log2;
-  const uint32_t qlo = (uint32_t)qmask, qhi = (uint32_t)(qmask >> 32);
   float m = kTreeNegBig, lsum = 0.0f;
   f32x16 o[C::DT];
 #pragma unroll
@@ -234,7 +168,7 @@ __global__ __launch_bounds__(KS * kTreeThreads, TreeCfg<D>::WAVES) void k_attn_t
     __syncthreads();  // every thread's loads have landed; the other buffer is free
     if (tile + KS < ntiles) issue(tile + KS, knext, vnext);
     const int tb = lo + tile * 64;
-    if (tb >= whi) return;  // (wave-uniform) past the wave's deepest query
+    if (tb >= q.hi) return;  // (wave-uniform) past the wave's deepest query
     // scores of both 32-key halves (two independent chains)
     f32x16 acc[2];
 #pragma unroll
@@ -248,31 +182,23 @@ __global__ __launch_bounds__(KS * kTreeThreads, TreeCfg<D>::WAVES) void k_attn_t
     // visibility of this lane's keys tb + 32 half + 8(v/4) + 4hh + v%4 for its row.  Depth never
     // decreases along the slots, so the tile's depth range is that of its first and last key.
     const int dfirst = __builtin_amdgcn_readlane(cdep, 0), dlast = __builtin_amdgcn_readlane(cdep, 63);
-    const bool all_visible = tb + 64 <= hi && tb + 64 <= h.n_shared && dlast <= wdmin &&
-                             (s.W <= 0 || wdmax - dfirst < s.W);
+    const bool all_visible = tb + 64 <= hi && tb + 64 <= h.n_shared && dlast <= q.dmin &&
+                             (s.W <= 0 || q.dmax - dfirst < s.W);
     if (!all_visible) {
-      // (branch-free per key: the test only selects)
       uint32_t vis[2] = {0, 0};
       if (tb + 64 <= h.n_shared) {
         // every key lies on every beam's path: the depth alone decides (the diagonal of a prefill)
 #pragma unroll
         for (int v = 0; v < 32; ++v) {
           const int i = 32 * (v >> 4) + 8 * (v % 16 >> 2) + 4 * hh + (v & 3);
-          const int dn = __builtin_amdgcn_ds_bpermute(i << 2, cdep);
-          const bool ok = (tb + i < hi) & (dn <= qdepth) & ((s.W <= 0) | (qdepth - dn < s.W));
-          vis[v >> 4] |= (uint32_t)ok << (v & 15);
+          vis[v >> 4] |= (uint32_t)tree_visible<false>(s, q, i, tb + i < hi, cdep, 0, 0) << (v & 15);
         }
       } else {
         const int mlo = (int)(uint32_t)cmk, mhi = (int)(uint32_t)(cmk >> 32);
 #pragma unroll
         for (int v = 0; v < 32; ++v) {
           const int i = 32 * (v >> 4) + 8 * (v % 16 >> 2) + 4 * hh + (v & 3);
-          const int dn = __builtin_amdgcn_ds_bpermute(i << 2, cdep);
-          const uint32_t lo_ = (uint32_t)__builtin_amdgcn_ds_bpermute(i << 2, mlo);
-          const uint32_t hi_ = (uint32_t)__builtin_amdgcn_ds_bpermute(i << 2, mhi);
-          const bool ok = (tb + i < hi) & (dn <= qdepth) & ((lo_ & qlo) == qlo) & ((hi_ & qhi) == qhi) &
-                          ((s.W <= 0) | (qdepth - dn < s.W));
-          vis[v >> 4] |= (uint32_t)ok << (v & 15);
+          vis[v >> 4] |= (uint32_t)tree_visible<true>(s, q, i, tb + i < hi, cdep, mlo, mhi) << (v & 15);
         }
       }
 #pragma unroll
@@ -283,7 +209,7 @@ __global__ __launch_bounds__(KS * kTreeThreads, TreeCfg<D>::WAVES) void k_attn_t
     const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
-      if (half == 1 && tb + 32 >= whi) return;  // (wave-uniform) past the wave's deepest query
+      if (half == 1 && tb + 32 >= q.hi) return;  // (wave-uniform) past the wave's deepest query
       // Probabilities relative to the row's shift m, rounded to bf16, and their sum over this
       // lane's 16 keys.  Softmax does not depend on the shift, so it needs no maximum: it only
       // has to keep the probabilities in range, and their sum says when it does not (a first
@@ -377,24 +303,7 @@ __global__ __launch_bounds__(KS * kTreeThreads, TreeCfg<D>::WAVES) void k_attn_t
     }
   }
 
-  // each wave writes its own rows: O / l (zero for a row without keys or without a query; a NaN
-  // score makes l NaN, and the row with it)
-  lsum += __shfl_xor(lsum, 32);
-  if (r < a.qmax * G) {
-    const bool some = row_ok && lsum != 0.0f;
-    const float inv = some ? 1.0f / lsum : 0.0f;
-    __bf16* orow = static_cast<__bf16*>(a.out) +
-                   ((((size_t)li * s.T + t) * a.qmax + owner) * s.Hq + g * G + r % G) * D;
-#pragma unroll
-    for (int dt = 0; dt < C::DT; ++dt)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        bf16x4 y;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) y[e] = (__bf16)(some ? o[dt][4 * q4 + e] * inv : 0.0f);
-        *reinterpret_cast<bf16x4*>(orow + 32 * dt + 8 * q4 + 4 * hh) = y;
-      }
-  }
+  tree_output<D>(s, a, u, q, G, hh, lsum, o);
 }
 
 }  // namespace

@@ -10,26 +10,15 @@
 // first weights (it takes no maximum) only pay over long chains.  Measured, 32 q / 8 KV heads at
 // d = 128, every node a query: 60 nodes 8.0 us here, 9.9 there; 200 nodes, 448 blocks, 19.4
 // and 20.7; 300 nodes, 80 blocks, 15.6 and 15.7; 1,000 nodes, 256 blocks, 35.4 and 28.1.
-#include "attn_common.h"
-#include "mfma_tile.h"
+#include "attn_tree_common.h"
 
 namespace td {
 
 namespace {
 
-constexpr int kTreeWaves = 4;  // (two WGs per CU: their barriers do not wait on each other)
-constexpr int kTreeThreads = kTreeWaves * 64;
-constexpr int kTreeRows = kTreeWaves * 32;  // query rows per WG
-constexpr float kTreeNegBig = -1.0e30f;
-constexpr float kTreeSlack = 8.0f;  // largest probability 2^8 before a row's shift moves
-
 template <int D>
-struct TreeCfg {
-  static constexpr int KSTEPS = D / 16;                 // 32x32x16 steps of S^T
-  static constexpr int DT = D / 32;                     // 32-wide d tiles of O^T
-  static constexpr int CPR = D / 8;                     // 16-byte chunks per node row
-  static constexpr int NBLK = CPR / 4;                  // 64-byte blocks per row
-  static constexpr int HALF = 32 * D * 2;               // bytes of 32 K (or V) rows
+struct TreeCfg : TreeGeom<D> {
+  using TreeGeom<D>::HALF;
   static constexpr int TILE = 4 * HALF;                 // K half 0, K half 1, V half 0, V half 1
   static constexpr int LOADS = TILE / 16 / kTreeThreads;  // 16-byte loads per thread per tile
   static_assert(TILE % (16 * kTreeThreads) == 0, "a tile is a whole number of WG loads");
@@ -40,66 +29,24 @@ __global__ __launch_bounds__(kTreeThreads, 2) void k_attn_tree_short(DevState s,
   using C = TreeCfg<D>;
   __shared__ __attribute__((aligned(16))) unsigned char lds[2 * C::TILE];
   __shared__ int wred[2][kTreeWaves];  // per wave: deepest query slot + 1, shallowest depth
-  // (trie, layer, KV head) unit and row block; the row blocks of a unit go to one XCD
-  int x = blockIdx.x, unit, rb;
-  if (a.xcd_group) {
-    const int xcd = x % 8, k = x / 8;
-    unit = (k / a.row_blocks) * 8 + xcd;
-    rb = a.row_blocks - 1 - k % a.row_blocks;
-  } else {
-    unit = x / a.row_blocks;
-    rb = a.row_blocks - 1 - x % a.row_blocks;
-  }
-  const int g = unit % s.Hkv, li = (unit / s.Hkv) % a.n_layers, t = unit / (s.Hkv * a.n_layers);
-  const TrieHdr h = s.hdr[t];
+  const TreeUnit u = tree_unit(s, a);
+  const TrieHdr h = s.hdr[u.t];
   const int N = h.n_nodes, base = h.base;
   const int G = s.Hq / s.Hkv;
-  const int lab = a.layer_begin + li;
+  const int lab = a.layer_begin + u.li;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = lane & 31, hh = lane >> 5;
-  const uint64_t* maskp = s.mask + (size_t)t * s.cap + base;
-  const int32_t* depthp = s.depth + (size_t)t * s.cap + base;
+  const uint64_t* maskp = s.mask + (size_t)u.t * s.cap + base;
+  const int32_t* depthp = s.depth + (size_t)u.t * s.cap + base;
 
-  // this lane's query row
-  const int r = rb * kTreeRows + wave * 32 + col;
-  const int owner = r / G;
-  int slot = r < a.qmax * G ? a.qslots[(size_t)t * a.qmax + owner] : -1;
-  bool row_ok = slot >= 0 && slot < N;
-  uint64_t qmask = 0;
-  int qdepth = -1;
-  if (row_ok) {
-    qmask = maskp[slot];
-    row_ok = qmask != 0ull;
-  }
-  if (row_ok) qdepth = depthp[slot];
-  const bool any_dead = __ballot(!row_ok) != 0ull;
-  // the wave's deepest query slot, shallowest and deepest query depth (live rows)
-  int whi = row_ok ? slot + 1 : 0, wdmin = row_ok ? qdepth : INT_MAX, wdmax = row_ok ? qdepth : -1;
-  for (int o = 16; o > 0; o >>= 1) {
-    whi = max(whi, __shfl_xor(whi, o));
-    wdmin = min(wdmin, __shfl_xor(wdmin, o));
-    wdmax = max(wdmax, __shfl_xor(wdmax, o));
-  }
-  whi = __builtin_amdgcn_readfirstlane(whi);
-  wdmin = __builtin_amdgcn_readfirstlane(wdmin);
-  wdmax = __builtin_amdgcn_readfirstlane(wdmax);
-  if (lane == 0) {
-    wred[0][wave] = whi;
-    wred[1][wave] = wdmin;
-  }
-  __syncthreads();
-  int hi = 0, dmin = INT_MAX;
-  for (int w = 0; w < kTreeWaves; ++w) {
-    hi = max(hi, wred[0][w]);
-    dmin = min(dmin, wred[1][w]);
-  }
-  // the block's key range: from the window start of its shallowest query to its deepest
-  // query slot (ancestors precede their descendants in slot order)
-  const int lo = hi > 0 ? window_lo(s, t, base, N, dmin) : 0;
+  const TreeRow q = tree_row(s, a, u, N, G, maskp, depthp, wave, col);
+  const bool any_dead = __ballot(!q.ok) != 0ull;
+  const int2 range = tree_range(s, u, q, base, N, lane, wave, wred);
+  const int lo = range.x, hi = range.y;
   const int ntiles = hi > lo ? (hi - lo + 63) / 64 : 0;
 
-  const __bf16* kpool = static_cast<const __bf16*>(s.k_pool) + pool_row(s, t, lab, g, base);
-  const __bf16* vpool = static_cast<const __bf16*>(s.v_pool) + pool_row(s, t, lab, g, base);
+  const __bf16* kpool = static_cast<const __bf16*>(s.k_pool) + pool_row(s, u.t, lab, u.g, base);
+  const __bf16* vpool = static_cast<const __bf16*>(s.v_pool) + pool_row(s, u.t, lab, u.g, base);
 
   // Load j of this thread writes LDS chunk c = kTreeThreads j + threadIdx.x of the tile: part c /
   // (HALF / 16) (K half 0, K half 1, V half 0, V half 1), row and physical chunk inside it;
@@ -135,25 +82,14 @@ __global__ __launch_bounds__(kTreeThreads, 2) void k_attn_tree_short(DevState s,
     kmk = maskp[nn];
   };
 
-  // this lane's query row (B operand of S^T): half hh of the row's d range
   bf16x8 qv[C::KSTEPS];
-  {
-    const uint4* qp = reinterpret_cast<const uint4*>(
-        static_cast<const __bf16*>(a.q) +
-        ((((size_t)li * s.T + t) * a.qmax + (row_ok ? owner : 0)) * s.Hq + g * G + r % G) * D + hh * (D / 2));
-#pragma unroll
-    for (int k = 0; k < C::KSTEPS; ++k) {
-      const uint4 v = row_ok ? qp[k] : make_uint4(0, 0, 0, 0);
-      qv[k] = __builtin_bit_cast(bf16x8, v);
-    }
-  }
+  tree_query<D>(s, a, u, q, G, hh, qv);
   // operand geometry (as in the decode kernel): K rows read in MFMA layout; V read back
   // transposed by 16-lane groups
   const int grp = lane >> 4, tm = (lane & 15) >> 2, tq = lane & 3;
   const int krow = col * (2 * D), kc0 = hh * (C::CPR / 2) + col;  // K operand k: chunk (kc0 + k) % CPR
 
   const float scale = a.scale_log2;
-  const uint32_t qlo = (uint32_t)qmask, qhi = (uint32_t)(qmask >> 32);
   float m = kTreeNegBig, lsum = 0.0f;
   f32x16 o[C::DT];
 #pragma unroll
@@ -175,7 +111,7 @@ __global__ __launch_bounds__(kTreeThreads, 2) void k_attn_tree_short(DevState s,
 #pragma unroll 1
     for (int half = 0; half < 2; ++half) {  // (not unrolled: one half's operands live at a time)
       const int hb = tb + half * 32;  // first key of the half
-      if (hb >= whi) continue;        // (wave-uniform) past the wave's deepest query
+      if (hb >= q.hi) continue;       // (wave-uniform) past the wave's deepest query
       const unsigned char* kh = kb + half * C::HALF;
       const __bf16* vh = reinterpret_cast<const __bf16*>(vb + half * C::HALF);
       bf16x8 kv[C::KSTEPS];
@@ -208,26 +144,20 @@ __global__ __launch_bounds__(kTreeThreads, 2) void k_attn_tree_short(DevState s,
       // key (lanes 32 half and 32 half + 31 hold them).
       const int dfirst = __builtin_amdgcn_readlane(cdep, 32 * half);
       const int dlast = __builtin_amdgcn_readlane(cdep, 32 * half + 31);
-      const bool all_visible = hb + 32 <= hi && hb + 32 <= h.n_shared && dlast <= wdmin &&
-                               (s.W <= 0 || wdmax - dfirst < s.W);
+      const bool all_visible = hb + 32 <= hi && hb + 32 <= h.n_shared && dlast <= q.dmin &&
+                               (s.W <= 0 || q.dmax - dfirst < s.W);
       if (all_visible) {
         if (any_dead) {
 #pragma unroll
-          for (int v = 0; v < 16; ++v) acc[v] = row_ok ? acc[v] : -INFINITY;
+          for (int v = 0; v < 16; ++v) acc[v] = q.ok ? acc[v] : -INFINITY;
         }
       } else {
-        // (branch-free: the test only selects)
         const int mlo = (int)(uint32_t)cmk, mhi = (int)(uint32_t)(cmk >> 32);
         uint32_t vis = 0;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int i = 32 * half + 8 * (v >> 2) + 4 * hh + (v & 3);
-          const int dn = __builtin_amdgcn_ds_bpermute(i << 2, cdep);
-          const uint32_t lo_ = (uint32_t)__builtin_amdgcn_ds_bpermute(i << 2, mlo);
-          const uint32_t hi_ = (uint32_t)__builtin_amdgcn_ds_bpermute(i << 2, mhi);
-          const bool ok = (tb + i < hi) & (dn <= qdepth) & ((lo_ & qlo) == qlo) & ((hi_ & qhi) == qhi) &
-                          ((s.W <= 0) | (qdepth - dn < s.W));
-          vis |= (uint32_t)ok << v;
+          vis |= (uint32_t)tree_visible<true>(s, q, i, tb + i < hi, cdep, mlo, mhi) << v;
         }
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[v] = (vis >> v) & 1u ? acc[v] : -INFINITY;
@@ -270,24 +200,7 @@ __global__ __launch_bounds__(kTreeThreads, 2) void k_attn_tree_short(DevState s,
     }
   }
 
-  // each wave writes its own rows: O / l (zero for a row without keys or without a query; a NaN
-  // score makes l NaN, and the row with it)
-  lsum += __shfl_xor(lsum, 32);
-  if (r < a.qmax * G) {
-    const bool some = row_ok && lsum != 0.0f;
-    const float inv = some ? 1.0f / lsum : 0.0f;
-    __bf16* orow = static_cast<__bf16*>(a.out) +
-                   ((((size_t)li * s.T + t) * a.qmax + owner) * s.Hq + g * G + r % G) * D;
-#pragma unroll
-    for (int dt = 0; dt < C::DT; ++dt)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        bf16x4 y;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) y[e] = (__bf16)(some ? o[dt][4 * q4 + e] * inv : 0.0f);
-        *reinterpret_cast<bf16x4*>(orow + 32 * dt + 8 * q4 + 4 * hh) = y;
-      }
-  }
+  tree_output<D>(s, a, u, q, G, hh, lsum, o);
 }
 
 }  // namespace

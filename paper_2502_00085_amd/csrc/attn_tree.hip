@@ -22,8 +22,8 @@
 //     their sum (needed anyway) tells: no maximum is taken;
 //   * a wave skips what lies past its deepest query; each wave owns its rows.
 //
-// Launches of few WGs (up to two per CU) make one WG of two groups, which take the tiles in
-// turn and merge their states at the end: the longest block's chain of tiles is halved.
+// Launches of few WGs (launch_attn_tree says how few) make one WG of two groups, which take the
+// tiles in turn and merge their states at the end: the longest block's chain of tiles is halved.
 // The row blocks of one (trie, layer, KV head) are placed on one XCD, so that its K/V rows
 // are read from HBM once and from that XCD's L2 afterwards.
 //

@@ -27,8 +27,9 @@
 // The row blocks of one (trie, layer, KV head) are placed on one XCD, so that its K/V rows
 // are read from HBM once and from that XCD's L2 afterwards.
 //
-// What bounds it: at two waves per SIMD neither pipe is full (matrix cores 35 % of the time,
-// vector ALU 42 %); leaving out the loads, the exponentials or most of the output products
+// What bounds it: at two waves per SIMD neither pipe is full (every node of a 2,070-node trie a
+// query, 32 layers: matrix cores busy 36 % of the time, 3,708 vector-ALU instructions per wave or
+// at least 32 %); leaving out the loads, the exponentials or most of the output products
 // shortens a tile by little more than their own time, so the waves' chains of score products,
 // softmax and output products are the limit.  A software pipeline of the three (scores of one
 // half beside the softmax of another) measured slower as hipcc schedules it.  Prefill of 2,096

@@ -41,8 +41,8 @@ HBM_PEAK_GBS = 8000.0
 ATTN_TRAFFIC = {
     "workload": "llama8b",
     "profile": "profiles/k_attn_mfma_llama8b_hbm_traffic.md",
-    "sources_sha256": "4d86f010c7daef700e6cd9f81802af3406a142bbe7ab1b8e5c48e919a2cc657b",
-    "bytes_per_launch": 275921664,    # 2.0 x 133,703.38 KiB FETCH_SIZE + 1.0 x 2,048 KiB WRITE_SIZE
+    "sources_sha256": "51f0e59c37836f29c86d52af1e2e49f34b915206f63e3ad34f00a5d685998a69",
+    "bytes_per_launch": 275921792,    # 2.0 x 133,703.44 KiB FETCH_SIZE + 1.0 x 2,048 KiB WRITE_SIZE
     "nodes_per_launch": 2070,         # attended nodes of the profiled (step-10) trie
     "qo_bytes_per_launch": 4194304,   # queries + outputs of the profiled launch
 }

@@ -31,6 +31,19 @@ def test_groups(d, tries, hkv, layers, g, prompt, n):
                    head_dim=d, beam_width=6, steps=3), seed=27, pick=lambda tr, r: every_node(tr, r)[-(n or 10 ** 6):])
 
 
+# a window over a trie of many nodes per level, queries in no order: a row block's keys are many more
+# than its window's levels hold on average (the estimate that chooses the kernel)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("window", [30, 100])
+def test_diverged_trie_with_unsorted_queries(d, window):
+    def shuffled(tr, g):
+        assert len(tr.order) > 900
+        return g.permutation(every_node(tr, g))
+
+    run_tree(small(n_layers=1, prompt_min=40, prompt_max=40, n_q_heads=8, n_kv_heads=2, head_dim=d, beam_width=16,
+                   steps=78, window=window, gc_interval=60, alpha=0.0), seed=28, pick=shuffled)
+
+
 @pytest.mark.parametrize("d,hkv", [(64, 2), (96, 4), (128, 2)])
 def test_large_scores(d, hkv, monkeypatch):
     # twelve times the usual scale: scores of a row over tens of powers of two
